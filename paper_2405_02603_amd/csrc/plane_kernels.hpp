@@ -108,8 +108,8 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
   __shared__ cx<T> pl[N * PP];
   const int tid = threadIdx.x;
   const int i0 = blockIdx.x;
-  const cx<T>* rho = reinterpret_cast<const cx<T>*>(a.items ? a.items[blockIdx.y].rho : a.in[blockIdx.y]);
-  cx<T>* S = reinterpret_cast<cx<T>*>(a.items ? a.items[blockIdx.y].work : a.out[blockIdx.y]);
+  const cx<T>* rho = reinterpret_cast<const cx<T>*>(a.items ? table_item(a.items, blockIdx.y).rho : a.in[blockIdx.y]);
+  cx<T>* S = reinterpret_cast<cx<T>*>(a.items ? table_item(a.items, blockIdx.y).work : a.out[blockIdx.y]);
   const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.twr);
   const cx<T>* pp = tw + tw_size(LC, PID);  // exp(-i pi k / n2)
 
@@ -243,8 +243,8 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
   __shared__ cx<T> pl[N * PP];
   const int tid = threadIdx.x;
   const int i0 = blockIdx.x;
-  const cx<T>* S = reinterpret_cast<const cx<T>*>(a.items ? a.items[blockIdx.y].work : a.in[blockIdx.y]);
-  cx<T>* phi = reinterpret_cast<cx<T>*>(a.items ? a.items[blockIdx.y].phi : a.out[blockIdx.y]);
+  const cx<T>* S = reinterpret_cast<const cx<T>*>(a.items ? table_item(a.items, blockIdx.y).work : a.in[blockIdx.y]);
+  cx<T>* phi = reinterpret_cast<cx<T>*>(a.items ? table_item(a.items, blockIdx.y).phi : a.out[blockIdx.y]);
   const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.twr);
   const cx<T>* pp = tw + tw_size(LC, PID);  // exp(-i pi k / n2)
 
@@ -269,8 +269,8 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
 #pragma unroll
       for (int r = 0; r < FC::R; ++r) {
         const unsigned row = 2 * (b + r * FC::NB);
-        e[j][r] = ok ? Sb[row * P + k] : czero<T>();
-        o[j][r] = ok ? Sb[(row + 1) * P + k] : czero<T>();
+        e[j][r] = ok ? ld(&Sb[row * P + k]) : czero<T>();
+        o[j][r] = ok ? ld(&Sb[(row + 1) * P + k]) : czero<T>();
       }
     }
   };
