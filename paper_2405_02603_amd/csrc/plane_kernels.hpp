@@ -44,6 +44,7 @@ struct PlaneArgs {
   const void* twr;   // twiddles of length n2 (plan PlaneCfg::pid) then exp(-i pi k / n2), k in [0, n2]
   long long plane;   // complex elements between S planes i0 (2 n1 P)
   int pitch;         // P
+  int stream;        // StreamBits
 };
 
 // Shape of the plane kernels for n1 == n2 == N: radix plan of length N (rows
@@ -219,15 +220,17 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
       if (half == 1) lds_barrier();  // the even transform's last stage has read the column
       cx<T> w[LC_::J][LC_::R];
       plane_column_fft<T, N, PID, false, NQC>(pl, tw, q, cidx, half == 0 ? ve : vo, w);
+      by_stream(a.stream & STREAM_COL_STORE, [&](auto sm) {
 #pragma unroll
-      for (int j = 0; j < LC_::J; ++j) {
-        const int b = q + NQC * j;
-        if (kok && ((LC_::NB % NQC == 0) || b < LC_::NB)) {
+        for (int j = 0; j < LC_::J; ++j) {
+          const int b = q + NQC * j;
+          if (kok && ((LC_::NB % NQC == 0) || b < LC_::NB)) {
 #pragma unroll
-          for (int m = 0; m < LC_::R; ++m)
-            put<T, PASS_COL_FWD>(&Sb[(2 * (b + m * LC_::NB) + half) * P + k], w[j][m]);
+            for (int m = 0; m < LC_::R; ++m)
+              put<sm.value>(&Sb[(2 * (b + m * LC_::NB) + half) * P + k], w[j][m]);
+          }
         }
-      }
+      });
     }
     lds_barrier();  // the next tile's lanes past n2 reuse columns of the first tile
   }
@@ -354,7 +357,7 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
       const int b = qr + NQR * j;
       if ((Li::NB % NQR == 0) || b < Li::NB) {
 #pragma unroll
-        for (int m = 0; m < Li::R / 2; ++m) put<T, PASS_ROW_INV>(&out[b + m * Li::NB], u[j][m]);
+        for (int m = 0; m < Li::R / 2; ++m) put<true>(&out[b + m * Li::NB], u[j][m]);
       }
     }
   }

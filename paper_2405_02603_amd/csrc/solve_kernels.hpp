@@ -28,6 +28,8 @@
 // consecutive elements of a row.
 #pragma once
 
+#include <type_traits>
+
 #include "fft_core.hpp"
 
 namespace fsp {
@@ -62,6 +64,7 @@ struct ColArgs {
   int nouter;                 // outer indices (P2/P4: n0; P3: n1 + 1 pairs)
   int n1;                     // P3: n1 (pairs k1 and 2 n1 - k1 share a Green's row)
   long long g_k1_stride;      // P3: reals between Green's blocks k1 (tiles (n0+1) TC)
+  int stream;                 // StreamBits
   int ntail;                  // P3: leading blocks that gather column ncols - 1 over TC k1 pairs
   int gather_min;             // P3 (host side): grid size from which the launcher gathers
   // P3 with several outputs from one item (the gradient solve; nout == 0 otherwise)
@@ -79,6 +82,7 @@ struct RowArgs {
   int nrows;                  // n0 * n1
   int n1;
   int pitch;                  // P
+  int stream;                 // StreamBits
   long long s_i0_stride;      // complex elements between S planes (2 n1 P)
 };
 
@@ -131,21 +135,70 @@ __device__ __forceinline__ cx<T> ld_once(const cx<T>* p) {
   return {w.x, w.y};
 }
 
-// Store of a pass result.  Results that the next pass does not re-read soon
-// are streamed past the caches (non-temporal); in float32 the axis-2 forward
-// pass and the axis-1 passes keep normal stores, because their output is
-// re-read by the next pass while part of it is still in the memory-side cache
-// (measured: streaming those is slower, streaming the others is faster).
-enum PassKind { PASS_ROW_FWD, PASS_COL_FWD, PASS_CONV, PASS_COL_INV, PASS_ROW_INV };
+// Which accesses of a solve are streamed past the caches (non-temporal).
+// Streaming what is not read again soon leaves the memory-side cache (256 MB)
+// to what is; where the spectra S of a launch group fit in it, streaming them
+// throws that away.  Measured (us; whole solves or batched steps, cached ->
+// streamed):
+//   Always: the loads of rho, the stores of the axis-0 pass and of phi.
+//   Never: the axis-1 passes' loads and the inverse axis-1 pass's stores (read
+//     next by the row pass: 256^3 float64 P4 + P5 222 -> 211 since cached).
+//   By the total of the group's S (StreamBits, set by the launcher):
+//     the axis-1 forward stores, from 200 MB: 256^3 float32 385 -> 370, sixteen
+//       128^3 833 -> 756, 512^3 float32 3553 -> 3442; below, 128^3 62.4 -> 63.3,
+//       192^3 float32 (123 MB) 172.8 -> 176.0.
+//     the inverse row loads, from 100 MB: 256^3 float64 P5 93 -> 75; below,
+//       128^3 62.4 -> 64.1, two 128^3 102.8 -> 106.5.
+//   By type and length:
+//     the forward row stores, rows of 384 and more (half of S is then beyond
+//       the cache at once): 512^3 float32 P1 + P2 1035 -> 986; 256^3 float32
+//       122 -> 135.
+//     the axis-0 loads, except float32 pencils of 512 and more: float64 256^3
+//       738 -> 717, 384^3 4710 -> 4470, sixteen float32 128^3 756 -> 737; but
+//       float32 512^3 3442 -> 3581.
+enum StreamBits {
+  STREAM_COL_STORE = 1,
+  STREAM_ROW_LOAD = 2
+};
+constexpr long long STREAM_COL_STORE_MIN = 200000000;  // bytes of S in the launch group
+constexpr long long STREAM_ROW_LOAD_MIN = 100000000;
 
-template <typename T, int KIND>
+__host__ __device__ constexpr bool stream_row_store(int n2) { return n2 >= 384; }
+template <typename T>
+__host__ __device__ constexpr bool stream_conv_load(int L) {
+  return sizeof(T) == 8 || L < 512;
+}
+
+template <bool STREAM, typename T>
+__device__ __forceinline__ cx<T> ld_as(const cx<T>* p) {
+  if constexpr (STREAM)
+    return ld_once(p);
+  else
+    return ld(p);
+}
+
+template <bool STREAM, typename T>
 __device__ __forceinline__ void put(cx<T>* p, cx<T> v) {
-  constexpr bool streamed = sizeof(T) == 8 || KIND == PASS_CONV || KIND == PASS_ROW_INV;
   const vec2<T> w = {v.x, v.y};
-  if constexpr (streamed)
+  if constexpr (STREAM)
     __builtin_nontemporal_store(w, (FSP_DEVICE_MEM vec2<T>*)p);
   else
     *(FSP_DEVICE_MEM vec2<T>*)p = w;
+}
+
+// f(true) or f(false) by a uniform flag of the launch.  The two are kept apart:
+// merged, their accesses would lose the streaming hint.
+template <class F>
+__device__ __forceinline__ void by_stream(bool stream, F f) {
+  if (stream) {
+    asm volatile("; streamed" ::: "memory");
+    f(std::true_type{});
+    asm volatile("; streamed" ::: "memory");
+  } else {
+    asm volatile("; cached" ::: "memory");
+    f(std::false_type{});
+    asm volatile("; cached" ::: "memory");
+  }
 }
 
 // LDS slot of element e of a row in the row passes: one pad slot after every
@@ -201,16 +254,25 @@ __global__ __launch_bounds__(TC* NQ) void k_col_fft(ColArgs a) {
     else
       dft_half_in<F::R, false, T>(v[j]);
   }
+  // the inverse pass's results are read next while in the memory-side cache
+  auto store = [&](auto f) {
+    if constexpr (INV)
+      f(std::false_type{});
+    else
+      by_stream(a.stream & STREAM_COL_STORE, f);
+  };
   if constexpr (K == 1) {
+    store([&](auto sm) {
 #pragma unroll
-    for (int j = 0; j < F::J; ++j) {
-      const int b = q + NQ * j;
-      if (cok && ((F::NB % NQ == 0) || b < F::NB)) {
+      for (int j = 0; j < F::J; ++j) {
+        const int b = q + NQ * j;
+        if (cok && ((F::NB % NQ == 0) || b < F::NB)) {
 #pragma unroll
-        for (int m = 0; m < F::R; ++m)
-          if (!INV || m < F::R / 2) put<T, INV ? PASS_COL_INV : PASS_COL_FWD>(&base[(b + m * F::NB) * rs], v[j][m]);
+          for (int m = 0; m < F::R; ++m)
+            if (!INV || m < F::R / 2) put<sm.value>(&base[(b + m * F::NB) * rs], v[j][m]);
+        }
       }
-    }
+    });
   } else {
     write_first_outputs<T, F::R, F::J, F::NB, NQ>(lds, v, q, idx);
     lds_barrier();
@@ -219,15 +281,17 @@ __global__ __launch_bounds__(TC* NQ) void k_col_fft(ColArgs a) {
     static_assert(!INV || Ls::R % 2 == 0, "inverse plans end with an even radix");
     cx<T> w[Ls::J][Ls::R];
     lds_last_stage<T, L, PID, REV, NQ, INV, false, INV>(lds, tw, q, idx, w);
+    store([&](auto sm) {
 #pragma unroll
-    for (int j = 0; j < Ls::J; ++j) {
-      const int b = q + NQ * j;
-      if (cok && ((Ls::NB % NQ == 0) || b < Ls::NB)) {
+      for (int j = 0; j < Ls::J; ++j) {
+        const int b = q + NQ * j;
+        if (cok && ((Ls::NB % NQ == 0) || b < Ls::NB)) {
 #pragma unroll
-        for (int m = 0; m < Ls::R; ++m)
-          if (!INV || m < Ls::R / 2) put<T, INV ? PASS_COL_INV : PASS_COL_FWD>(&base[(b + m * Ls::NB) * rs], w[j][m]);
+          for (int m = 0; m < Ls::R; ++m)
+            if (!INV || m < Ls::R / 2) put<sm.value>(&base[(b + m * Ls::NB) * rs], w[j][m]);
+        }
       }
-    }
+    });
   }
 }
 
@@ -365,7 +429,7 @@ __global__ __launch_bounds__(TC* NQ, WPE) void k_col_conv(ColArgs a) {
       for (int r = 0; r < F::R / 2; ++r) raw[j][r] = czero<T>();
       if (ok) {  // one branch around the butterfly's loads
 #pragma unroll
-        for (int r = 0; r < F::R / 2; ++r) raw[j][r] = ld_once(&base[(b + r * F::NB) * rs]);
+        for (int r = 0; r < F::R / 2; ++r) raw[j][r] = ld_as<stream_conv_load<T>(L)>(&base[(b + r * F::NB) * rs]);
       }
     }
   };
@@ -395,7 +459,7 @@ __global__ __launch_bounds__(TC* NQ, WPE) void k_col_conv(ColArgs a) {
         const int b = q + NQ * j;
         if (st && ((Lf::NB % NQ == 0) || b < Lf::NB)) {
 #pragma unroll
-          for (int m = 0; m < Lf::R / 2; ++m) put<T, PASS_CONV>(&base[(b + m * Lf::NB) * rs], x[j][m]);
+          for (int m = 0; m < Lf::R / 2; ++m) put<true>(&base[(b + m * Lf::NB) * rs], x[j][m]);
         }
       }
     } else {
@@ -415,7 +479,7 @@ __global__ __launch_bounds__(TC* NQ, WPE) void k_col_conv(ColArgs a) {
         const int b = q + NQ * j;
         if (st && ((Li::NB % NQ == 0) || b < Li::NB)) {
 #pragma unroll
-          for (int m = 0; m < Li::R / 2; ++m) put<T, PASS_CONV>(&base[(b + m * Li::NB) * rs], u[j][m]);
+          for (int m = 0; m < Li::R / 2; ++m) put<true>(&base[(b + m * Li::NB) * rs], u[j][m]);
         }
       }
     }
@@ -550,7 +614,11 @@ __global__ __launch_bounds__(TC* NQ) void k_col_conv_pipe(ColArgs a) {
       const int b = q + NQ * j;
       const bool ok = on && ((F::NB % NQ == 0) || b < F::NB);
 #pragma unroll
-      for (int r = 0; r < F::R / 2; ++r) raw[j][r] = ok ? ld_once(&base[(b + r * F::NB) * rs]) : czero<T>();
+      for (int r = 0; r < F::R / 2; ++r) raw[j][r] = czero<T>();
+      if (ok) {
+#pragma unroll
+        for (int r = 0; r < F::R / 2; ++r) raw[j][r] = ld_as<stream_conv_load<T>(L)>(&base[(b + r * F::NB) * rs]);
+      }
     }
   };
   auto run_set = [&](cx<T>* base, const T* g, bool on, const cx<T> (&raw)[F::J][F::R / 2]) {
@@ -589,7 +657,7 @@ __global__ __launch_bounds__(TC* NQ) void k_col_conv_pipe(ColArgs a) {
       const int b = q + NQ * j;
       if (on && ((Li::NB % NQ == 0) || b < Li::NB)) {
 #pragma unroll
-        for (int m = 0; m < Li::R / 2; ++m) put<T, PASS_CONV>(&base[(b + m * Li::NB) * rs], u[j][m]);
+        for (int m = 0; m < Li::R / 2; ++m) put<true>(&base[(b + m * Li::NB) * rs], u[j][m]);
       }
     }
   };
@@ -826,7 +894,7 @@ __global__ __launch_bounds__(NT) void k_slab_conv(SlabArgs a) {
   for (int e = tid; e < N0 * N1 * TC; e += NT) {
     const int c = e % TC, i1 = (e / TC) % N1, i0 = e / (TC * N1);
     const int col = col0 + c;
-    if (col < a.ncols) put<T, PASS_COL_INV>(&S[i0 * a.plane + (long long)i1 * a.pitch + col], lds[(i0 * L1 + i1) * TC + c]);
+    if (col < a.ncols) put<false>(&S[i0 * a.plane + (long long)i1 * a.pitch + col], lds[(i0 * L1 + i1) * TC + c]);
   }
 }
 
@@ -912,7 +980,7 @@ __global__ __launch_bounds__(TR* NQ) void k_row_r2c(RowArgs a) {
           const cx<T> E = {T(0.5) * (A.x + B.x), T(0.5) * (A.y + B.y)};
           const cx<T> D = {T(0.5) * (A.x - B.x), T(0.5) * (A.y - B.y)};
           const cx<T> U = cmul(pp[k], D);
-          put<T, PASS_ROW_FWD>(&out[k], cx<T>{E.x + U.y, E.y - U.x});
+          put<stream_row_store(LC)>(&out[k], cx<T>{E.x + U.y, E.y - U.x});
         }
       }
     }
@@ -943,11 +1011,13 @@ __global__ __launch_bounds__(TR* NQ) void k_row_c2r(RowArgs a) {
     const void* src = a.items ? table_item(a.items, blockIdx.y).work : a.in[blockIdx.y];
     const cx<T>* in = reinterpret_cast<const cx<T>*>(src) + (long long)i0 * a.s_i0_stride + (long long)i1 * a.pitch;
     issue_fence();
+    by_stream(a.stream & STREAM_ROW_LOAD, [&](auto sm) {
 #pragma unroll
-    for (int j = 0; j < JI; ++j) {
-      const int k = q + NQ * j;
-      raw[g][j] = (rok && k <= LC) ? ld_once(&in[k]) : czero<T>();
-    }
+      for (int j = 0; j < JI; ++j) {
+        const int k = q + NQ * j;
+        raw[g][j] = (rok && k <= LC) ? ld_as<sm.value>(&in[k]) : czero<T>();
+      }
+    });
   }
   issue_fence();
   const cx<T>* pp = tw + tw_size(LC, PID);
@@ -993,7 +1063,7 @@ __global__ __launch_bounds__(TR* NQ) void k_row_c2r(RowArgs a) {
           const int b = q + NQ * j;
           if ((F::NB % NQ == 0) || b < F::NB) {
 #pragma unroll
-            for (int m = 0; m < F::R / 2; ++m) put<T, PASS_ROW_INV>(&out[b + m * F::NB], v[j][m]);
+            for (int m = 0; m < F::R / 2; ++m) put<true>(&out[b + m * F::NB], v[j][m]);
           }
         }
       }
@@ -1012,7 +1082,7 @@ __global__ __launch_bounds__(TR* NQ) void k_row_c2r(RowArgs a) {
           const int b = q + NQ * j;
           if ((Li::NB % NQ == 0) || b < Li::NB) {
 #pragma unroll
-            for (int m = 0; m < Li::R / 2; ++m) put<T, PASS_ROW_INV>(&out[b + m * Li::NB], u[j][m]);
+            for (int m = 0; m < Li::R / 2; ++m) put<true>(&out[b + m * Li::NB], u[j][m]);
           }
         }
       }

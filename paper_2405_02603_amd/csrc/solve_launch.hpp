@@ -387,8 +387,13 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   if (!tab && (g.items < 1 || g.items > MAX_ITEMS)) return hipErrorInvalidValue;
   if (tab && (g.items < 1 || g.items > 65535 || g.nout)) return hipErrorInvalidValue;
   const int nfill = tab ? 0 : g.items;
+  // spectra of this group together: what the caches would have to hold
+  const long long s_bytes = (long long)(g.nout ? g.nout : g.items) * g.n0 * plane * (long long)sizeof(cx<T>);
+  const int stream = (s_bytes >= STREAM_COL_STORE_MIN ? STREAM_COL_STORE : 0) |
+                     (s_bytes >= STREAM_ROW_LOAD_MIN ? STREAM_ROW_LOAD : 0);
   RowArgs ra{};
   ra.items = g.items_dev;
+  ra.stream = stream;
   ra.nrows = g.n0 * g.n1;
   ra.n1 = g.n1;
   ra.pitch = g.pitch;
@@ -397,6 +402,7 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   // P2 / P4: pencils along axis 1; outer = i0
   ColArgs ca{};
   ca.items = g.items_dev;
+  ca.stream = stream;
   for (int i = 0; i < nfill; ++i) ca.data[i] = g.work[i];
   ca.ncols = g.n2 + 1;
   ca.row_stride = P;
@@ -443,6 +449,7 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   const bool plane_fwd = g.var[0] == PLANE, plane_inv = g.var[3] == PLANE;
   PlaneArgs pa{};
   pa.items = g.items_dev;
+  pa.stream = stream;
   pa.plane = plane;
   pa.pitch = g.pitch;
   auto run = [&](int pass, int c0, int c1) -> hipError_t {
