@@ -119,7 +119,8 @@ fsp_status fsp_plan_bytes(fsp_plan p, size_t* ghat_bytes, size_t* work_bytes);
  * the caller's stream order); reported for admission control.  This is the
  * pre-computation grid of Sections 2.3 and 2.4 in float64: (4N)^3 samples for
  * FSP_VICO, (2N+1)^3 for FSP_VICO_DCT (the memory reduction of Section 2.4),
- * (N+1)^3 for FSP_HOCKNEY, plus one intermediate of the per-axis transforms. */
+ * (N+1)^3 for FSP_HOCKNEY, plus one intermediate of the per-axis transforms; at
+ * most that (a potential on open axes, and FSP_HOCKNEY, never store that grid). */
 fsp_status fsp_plan_precompute_bytes(fsp_plan p, size_t* bytes);
 
 /* Attach device memory.  ghat_dev / work_dev are caller-owned device buffers
@@ -152,7 +153,8 @@ fsp_status fsp_plan_share_ghat(fsp_plan dst, fsp_plan src);
  *     inverse transformed and restricted to the doubled grid, then as above.
  *   FSP_VICO_DCT: Section 2.4 -- eq. (3) sampled on its (2N+1)^3 unique
  *     values, inverse transformed by a DCT-I of length 2 n_d + 1 per axis
- *     keeping the doubled grid's octant, then as above.
+ *     keeping the doubled grid's octant, then as above (the potential on open
+ *     axes: both transforms of an axis as one product).
  * Every per-axis transform is a dense float64 cosine (or sine) contraction
  * run by this library's own kernels.  The result is reused by every later
  * solve (Section 2.3); calling this again recomputes it (a refresh, needed

@@ -18,13 +18,13 @@
 
 #include "fft_core.hpp"
 #include "fsp.h"
+#include "greens_axis.hpp"
 #include "internal.hpp"
 #include "solve_launch.hpp"
 
 namespace fsp {
 hipError_t solve_f32(const SolveGeom& g, int first, int last, hipStream_t s);
 hipError_t solve_f64(const SolveGeom& g, int first, int last, hipStream_t s);
-hipError_t greens_he_kernel(double* K, const int n[3], const double h[3], double g0, hipStream_t s);
 hipError_t greens_he_grad_kernel(double* D, const int n[3], const double h[3], int axis, hipStream_t s);
 hipError_t greens_vico_spectrum(double* G, const int samples[3], const double f[3], double L, bool fft_order,
                                 hipStream_t s);
@@ -686,6 +686,15 @@ static void component_matrices(const fsp_plan_s* p, int comp, std::vector<double
   }
 }
 
+// Whether the potential's transform is computed in three axis passes
+// (greens_axis.hpp): the Hockney-Eastwood kernel on any axes (its offsets fold
+// to the nearest image as they are sampled), the modified Vico-Greengard route
+// on open axes (a periodic axis folds the kernel between the two transforms
+// that the axis matrix merges).
+static bool by_axes(const fsp_plan_s* p) {
+  return p->d.greens == FSP_HOCKNEY || (p->d.greens == FSP_VICO_DCT && !p->periodic);
+}
+
 fsp_status fsp_precompute(fsp_plan p, void* stream) {
   if (!p) return fail(FSP_ERR_INVALID_ARG, "fsp_precompute: NULL plan");
   if (!p->bound) return fail(FSP_ERR_NOT_READY, "fsp_precompute: bind buffers first");
@@ -696,15 +705,25 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
   const int* n = p->n;
   const int gk = p->d.greens;
   const int ncomp = p->grad ? 4 : 1;
-  // all components' matrices, uploaded once (the host image outlives the copy)
+  const bool axes = by_axes(p);  // component 0 in three axis passes
+  const int first = axes ? 1 : 0;
+  // the other components' matrices, uploaded once (the host image outlives the copy)
   std::vector<double>& cm = p->cmat_host;
   cm.clear();
   std::vector<AxisOp> ops;
-  for (int c = 0; c < ncomp; ++c) component_matrices(p, c, cm, ops);
-  const size_t per_comp = ops.size() / ncomp;
+  for (int c = first; c < ncomp; ++c) component_matrices(p, c, cm, ops);
+  const size_t per_comp = ncomp > first ? ops.size() / (ncomp - first) : 0;
   const size_t n0 = n[0], n1 = n[1], n2 = n[2];
   size_t a_elems, b_elems;
-  if (gk == FSP_HOCKNEY) {
+  // axis passes: rows of the arrays between them; Vico-Greengard's, of 2 n2 + 1
+  // values, are padded to whole 128-byte lines (each array still fits where the
+  // (2n+1)^3 samples, here never stored, and their first transform would be)
+  const size_t d1 = gk == FSP_HOCKNEY ? n1 + 1 : 2 * n1 + 1;
+  const size_t p2 = gk == FSP_HOCKNEY ? n2 + 1 : align_up(2 * n2 + 1, 16);
+  if (axes && ncomp == 1) {
+    a_elems = (n0 + 1) * d1 * p2;
+    b_elems = (n0 + 1) * (n1 + 1) * p2;
+  } else if (gk == FSP_HOCKNEY) {
     a_elems = b_elems = (n0 + 1) * (n1 + 1) * (n2 + 1);
   } else if (gk == FSP_VICO_DCT) {
     a_elems = (2 * n0 + 1) * (2 * n1 + 1) * (2 * n2 + 1);
@@ -713,20 +732,64 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
     a_elems = 64 * n0 * n1 * n2;
     b_elems = 16 * n1 * n2 * (n0 + 1);
   }
-  double *A = nullptr, *B = nullptr, *C = nullptr;
-  e = hipMallocAsync((void**)&A, a_elems * 8, s);
-  if (e == hipSuccess) e = hipMallocAsync((void**)&B, b_elems * 8, s);
-  if (e == hipSuccess) e = hipMallocAsync((void**)&C, cm.size() * 8, s);
+  size_t c_elems = cm.size();
+  size_t image[3] = {0, 0, 0};  // axis passes: each axis's matrix image in C (equal axes share one)
+  if (axes)
+    for (int a = 0; a < 3; ++a) {
+      const int same = a > 0 && n[a] == n[0] ? 0 : a > 1 && n[a] == n[1] ? 1 : a;
+      if (same < a) {
+        image[a] = image[same];
+      } else {
+        image[a] = c_elems;
+        c_elems += fsp::green_axis_image_elems(n[a]);
+      }
+    }
+  // one transient buffer: A, B and the matrices
+  const size_t a_off = 0, b_off = align_up(a_elems, 32), c_off = b_off + align_up(b_elems, 32);
+  double* T = nullptr;
+  e = hipMallocAsync((void**)&T, (c_off + c_elems) * 8, s);
   if (e != hipSuccess) {
     (void)hipGetLastError();
-    if (A) (void)hipFreeAsync(A, s);
-    if (B) (void)hipFreeAsync(B, s);
     return fail(FSP_ERR_OUT_OF_MEMORY, "fsp_precompute: transient float64 buffers could not be allocated");
   }
+  double *const A = T + a_off, *const B = T + b_off, *const C = T + c_off;
   p->ready = false;
-  e = hipMemcpyAsync(C, cm.data(), cm.size() * 8, hipMemcpyHostToDevice, s);
-  for (int comp = 0; comp < ncomp && e == hipSuccess; ++comp) {
-    size_t mi = comp * per_comp;
+  if (!cm.empty()) e = hipMemcpyAsync(C, cm.data(), cm.size() * 8, hipMemcpyHostToDevice, s);
+  if (axes && e == hipSuccess) {
+    const bool vico = gk == FSP_VICO_DCT;
+    for (int a = 0; a < 3 && e == hipSuccess; ++a)
+      if ((a == 0 || image[a] != image[0]) && (a < 2 || image[a] != image[1]))
+        e = fsp::green_axis_image(C + image[a], n[a], vico, s);
+    fsp::AxisArgs g{};
+    g.n0 = n[0];
+    g.n1 = n[1];
+    g.n2 = n[2];
+    g.d1 = (int)d1;
+    g.p2 = (int)p2;
+    g.octant = static_cast<char*>(p->ghat) + p->oct_off;
+    g.tile = p->gtile;
+    g.f64 = p->d.prec == FSP_F64;
+    g.scale = p->V / (8.0 * n0 * n1 * n2);
+    if (vico) g.scale /= 64.0 * n0 * n1 * n2 * p->V;
+    for (int a = 0; a < 3; ++a) g.f[a] = vico ? M_PI / (2.0 * n[a] * p->h[a]) : p->h[a];
+    g.half_turns = (double)((long double)p->L / (2.0L * 3.141592653589793238462643383279502884L));
+    g.at_zero = 0.5 * p->L * p->L;
+    g.g0 = p->g0;
+    g.periodic = p->periodic;
+    const double* in[3] = {nullptr, A, B};
+    double* out[3] = {A, B, nullptr};
+    const int cols[3] = {g.d1 * g.p2, (n[0] + 1) * g.p2, (n[0] + 1) * (n[1] + 1)};
+    for (int a = 0; a < 3 && e == hipSuccess; ++a) {
+      g.image = C + image[a];
+      g.x = in[a];
+      g.y = out[a];
+      g.n = n[a];
+      g.N = cols[a];
+      e = fsp::green_axis(g, vico, a, s);
+    }
+  }
+  for (int comp = first; comp < ncomp && e == hipSuccess; ++comp) {
+    size_t mi = (comp - first) * per_comp;
     long long dims[3];  // current layout dims, leading axis first
     double scale = p->V / (8.0 * n0 * n1 * n2);  // folds V and the 1/M^3 of the inverse transform
     double* X = A;
@@ -743,10 +806,7 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
       std::swap(X, Y);
     };
     if (gk == FSP_HOCKNEY) {
-      if (comp == 0)
-        e = fsp::greens_he_kernel(X, n, p->h, p->g0, s);
-      else
-        e = fsp::greens_he_grad_kernel(X, n, p->h, comp - 1, s);
+      e = fsp::greens_he_grad_kernel(X, n, p->h, comp - 1, s);
       dims[0] = n0 + 1;
       dims[1] = n1 + 1;
       dims[2] = n2 + 1;
@@ -763,7 +823,7 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
       dims[1] = samples[1];
       dims[2] = samples[2];
       for (int a = 0; a < 3; ++a) contract(n[a] + 1);
-      // inverse transform on the 4n grid: 1 / prod(4 n_d h_d) = 1 / (64 n0 n1 n2 V)
+    // inverse transform on the 4n grid: 1 / prod(4 n_d h_d) = 1 / (64 n0 n1 n2 V)
       scale /= 64.0 * n0 * n1 * n2 * p->V;
     }
     if (p->periodic && e == hipSuccess) {  // the kernel octant (in X) folded to the nearest image
@@ -776,9 +836,7 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
       e = fsp::greens_store_octant(X, static_cast<char*>(p->ghat) + off, p->d.prec == FSP_F64, n, p->gtile, scale, s);
   }
   if (e == hipSuccess) e = hipMemcpyAsync(p->ghat, p->tw_host.data(), p->tw_host.size(), hipMemcpyHostToDevice, s);
-  (void)hipFreeAsync(A, s);
-  (void)hipFreeAsync(B, s);
-  (void)hipFreeAsync(C, s);
+  (void)hipFreeAsync(T, s);
   if (e != hipSuccess) return fail_hip(e, "fsp_precompute");
   p->ghat_read = p->ghat;
   p->ready = true;

@@ -3,18 +3,19 @@
 // Every route ends in the same object: the transform of the mirror-extended
 // real-space kernel on the octant k in [0, n] (real and even, so the octant
 // holds all of it), scaled by V / (8 n0 n1 n2) and rounded once to the solve
-// precision.
+// precision.  The potential's transform for Hockney-Eastwood and for
+// Vico-Greengard on open axes is made in three axis passes (greens_axis.hip);
+// here are the routes that keep their transforms apart:
 //
-//   Hockney-Eastwood (Section 2.2): K[m] = 1/(4 pi |m h|), K[0] = g0, then a
-//     DCT-I of length n_d + 1 on each axis.
-//   Vico-Greengard, modified (Section 2.4): the kernel of eq. (3) sampled at the
-//     (2n+1)^3 non-negative frequencies of the 4n grid, a DCT-I of length
-//     2 n_d + 1 on each axis keeping only outputs m_d <= n_d (that is the
-//     restriction to the doubled grid), then as Hockney-Eastwood.
+//   Vico-Greengard, modified (Section 2.4), with periodic axes: the kernel of
+//     eq. (3) sampled at the (2n+1)^3 non-negative frequencies of the 4n grid, a
+//     DCT-I of length 2 n_d + 1 on each axis keeping only outputs m_d <= n_d
+//     (that is the restriction to the doubled grid), the fold to the nearest
+//     images, then a DCT-I of length n_d + 1 on each axis.
 //   Vico-Greengard, original (Section 2.3): eq. (3) sampled on the full
 //     (4n)^3 frequency grid, the inverse transform on that grid evaluated at
 //     the octant outputs m_d <= n_d only (a real cosine sum, since the grid
-//     data are real and even), then as Hockney-Eastwood.
+//     data are real and even), then a DCT-I of length n_d + 1 on each axis.
 //
 // Derivative tables (the kernel's derivative along axis a, odd along a): the
 // same steps with sine forms along a -- -k_a-weighted sine sums from the
@@ -32,20 +33,6 @@
 #include <vector>
 
 namespace fsp {
-
-__global__ __launch_bounds__(256) void k_he_kernel(double* K, int n0, int n1, int n2, double h0, double h1,
-                                                   double h2, double g0) {
-  const long long total = (long long)(n0 + 1) * (n1 + 1) * (n2 + 1);
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const int m2 = (int)(i % (n2 + 1));
-  const long long t = i / (n2 + 1);
-  const int m1 = (int)(t % (n1 + 1));
-  const int m0 = (int)(t / (n1 + 1));
-  const double x = m0 * h0, y = m1 * h1, z = m2 * h2;
-  const double r = sqrt(x * x + y * y + z * z);
-  K[i] = (i == 0) ? g0 : 1.0 / (4.0 * M_PI * r);
-}
 
 // Derivative of the Hockney-Eastwood kernel along `axis` on the octant:
 // D[m] = -x_a / (4 pi |x|^3), x = m h, with 0 (an odd function's value) at m = 0.
@@ -134,12 +121,6 @@ __global__ __launch_bounds__(256) void k_store_octant(const double* __restrict__
 
 // ------------------------------------------------------------------ host side
 static unsigned grid1(long long n) { return (unsigned)((n + 255) / 256); }
-
-hipError_t greens_he_kernel(double* K, const int n[3], const double h[3], double g0, hipStream_t s) {
-  const long long total = (long long)(n[0] + 1) * (n[1] + 1) * (n[2] + 1);
-  hipLaunchKernelGGL(k_he_kernel, dim3(grid1(total)), dim3(256), 0, s, K, n[0], n[1], n[2], h[0], h[1], h[2], g0);
-  return hipGetLastError();
-}
 
 hipError_t greens_he_grad_kernel(double* D, const int n[3], const double h[3], int axis, hipStream_t s) {
   const long long total = (long long)(n[0] + 1) * (n[1] + 1) * (n[2] + 1);
