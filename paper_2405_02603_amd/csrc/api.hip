@@ -288,31 +288,68 @@ struct fsp_plan_s {
 
 namespace {
 
+// The twiddle tables of one axis for every radix plan, each plan's from a
+// multiple of 256 bytes.
+enum TwiddleRole { TW_ROW, TW_AXIS1, TW_AXIS0 };
+struct TwiddlePart {
+  std::vector<char> bytes;
+  size_t off[fsp::NUM_PLANS];
+};
+
 template <typename T>
-void build_twiddles(fsp_plan_s* p) {
-  std::vector<char>& b = p->tw_host;
-  b.clear();
+TwiddlePart make_twiddles(TwiddleRole role, int n) {
+  TwiddlePart w;
+  std::vector<char>& b = w.bytes;
   for (int pid = 0; pid < fsp::NUM_PLANS; ++pid) {
-    p->tw_row_off[pid] = b.size();
-    append_twiddles<T>(b, p->n[2], pid);
-    for (int k = 0; k <= p->n[2]; ++k) {  // split table exp(-i pi k / n2)
-      long double c, s;
-      cis_neg(k, 2LL * p->n[2], &c, &s);
-      push_c<T>(b, c, s);
+    w.off[pid] = b.size();
+    if (role == TW_ROW) {
+      append_twiddles<T>(b, n, pid);
+      for (int k = 0; k <= n; ++k) {  // split table exp(-i pi k / n2)
+        long double c, s;
+        cis_neg(k, 2LL * n, &c, &s);
+        push_c<T>(b, c, s);
+      }
+    } else {
+      append_twiddles<T>(b, 2 * n, pid);
+      if (role == TW_AXIS0) append_full_twiddles<T>(b, 2 * n, pid);  // read by the axis-0 kernel's LDS-table variant
     }
     b.resize(align_up(b.size(), 256), 0);
   }
-  for (int pid = 0; pid < fsp::NUM_PLANS; ++pid) {
-    p->tw_c1_off[pid] = b.size();
-    append_twiddles<T>(b, 2 * p->n[1], pid);
-    b.resize(align_up(b.size(), 256), 0);
+  return w;
+}
+
+// A table depends on its role, length and precision only: at most one of each
+// is made per process and shared by the plans built later (making them is all
+// of fsp_plan_create's time, 128^3 561 -> 3 us, which a program that fits its
+// box to every step pays each time).  Three roles, two precisions and thirteen
+// lengths bound what is kept.
+std::mutex g_twiddle_mu;
+std::map<std::tuple<int, int, bool>, std::shared_ptr<const TwiddlePart>> g_twiddles;
+
+std::shared_ptr<const TwiddlePart> twiddles(TwiddleRole role, int n, bool f64) {
+  const auto key = std::make_tuple((int)role, n, f64);
+  {
+    std::lock_guard<std::mutex> lk(g_twiddle_mu);
+    auto it = g_twiddles.find(key);
+    if (it != g_twiddles.end()) return it->second;
   }
-  for (int pid = 0; pid < fsp::NUM_PLANS; ++pid) {
-    p->tw_c0_off[pid] = b.size();
-    append_twiddles<T>(b, 2 * p->n[0], pid);
-    append_full_twiddles<T>(b, 2 * p->n[0], pid);  // read by the axis-0 kernel's LDS-table variant
-    b.resize(align_up(b.size(), 256), 0);
-  }
+  auto w = std::make_shared<const TwiddlePart>(f64 ? make_twiddles<double>(role, n) : make_twiddles<float>(role, n));
+  std::lock_guard<std::mutex> lk(g_twiddle_mu);
+  return g_twiddles.emplace(key, w).first->second;
+}
+
+void build_twiddles(fsp_plan_s* p) {
+  const bool f64 = p->d.prec == FSP_F64;
+  std::vector<char>& b = p->tw_host;
+  b.clear();
+  auto add = [&](TwiddleRole role, int n, size_t* off) {
+    const auto w = twiddles(role, n, f64);
+    for (int pid = 0; pid < fsp::NUM_PLANS; ++pid) off[pid] = b.size() + w->off[pid];
+    b.insert(b.end(), w->bytes.begin(), w->bytes.end());
+  };
+  add(TW_ROW, p->n[2], p->tw_row_off);
+  add(TW_AXIS1, p->n[1], p->tw_c1_off);
+  add(TW_AXIS0, p->n[0], p->tw_c0_off);
   p->oct_off = b.size();
 }
 
@@ -423,10 +460,12 @@ fsp_status fsp_plan_create(const fsp_plan_desc* desc, fsp_plan* out) {
   p->rb = d.prec == FSP_F64 ? 8 : 4;
   const int cb = 2 * p->rb;
   p->pitch = (int)align_up((size_t)p->n[2] + 1, 128 / cb);
-  if (d.prec == FSP_F64)
-    build_twiddles<double>(p);
-  else
-    build_twiddles<float>(p);
+  try {
+    build_twiddles(p);
+  } catch (const std::bad_alloc&) {
+    delete p;
+    return fail(FSP_ERR_OUT_OF_MEMORY, "fsp_plan_create: host allocation failed");
+  }
   p->gtile = d.prec == FSP_F64 ? fsp::conv_tile_f64(2 * p->n[0]) : fsp::conv_tile_f32(2 * p->n[0]);
   {
     const size_t tiles = (p->n[2] + 1 + p->gtile - 1) / p->gtile;
