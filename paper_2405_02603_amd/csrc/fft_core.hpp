@@ -35,8 +35,8 @@ struct RadixPlan {
 
 // Radix sequences for each supported pencil length (2^a or 3 * 2^a, 8..1024).
 // Plan 0 is the default; plan 1 is an alternative (fewer, larger stages or
-// more, smaller ones) the autotuner may pick: at 96, 192 and 384 it is the
-// two-stage plan ending in radix 12 or 24, one LDS exchange fewer than plan 0.
+// more, smaller ones): at 96, 192, 384 and 768 it is the two-stage plan ending
+// in radix 12 or 24, one LDS exchange fewer than plan 0.
 // The first radix is always even and divides 32.
 constexpr int NUM_PLANS = 2;
 
@@ -56,7 +56,7 @@ __host__ __device__ constexpr RadixPlan radix_plan(int L, int pid = 0) {
       case 256: return {3, {8, 4, 8, 0}};
       case 384: return {2, {16, 24, 0, 0}};
       case 512: return {3, {8, 8, 8, 0}};
-      case 768: return {4, {16, 4, 4, 3}};
+      case 768: return {2, {32, 24, 0, 0}};
       case 1024: return {3, {16, 8, 8, 0}};
       default: return {0, {0, 0, 0, 0}};
     }

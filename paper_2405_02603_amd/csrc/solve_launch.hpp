@@ -15,7 +15,13 @@ struct TileCfg {
 };
 
 // Schedule variants per pencil length; variant 0 is the default and the
-// autotuner may pick another.  Column passes of one length share TC (the
+// autotuner may pick another.  Plans that no one tuned run variant 0 (a served
+// request, a box fitted to each step), so it is the shape measured fastest in
+// single cube solves.  Before that, lengths 3 * 2^a kept their three-stage
+// plans there; whole untuned solves, us: 24^3 float32 35.7 -> 24.6, 48^3 42.8
+// -> 27.4, 96^3 50.8 -> 40.3, 192^3 271 -> 172, 384^3 2260 -> 1491; float64
+// 24^3 46.0 -> 24.0, 48^3 48.5 -> 29.8, 96^3 79.4 -> 60.4, 192^3 462 -> 330,
+// 384^3 5330 -> 3042.  Column passes of one length share TC (the
 // Green's octant is stored in tiles of the axis-0 pass's TC).
 constexpr int NUM_VARIANTS = 3;
 
@@ -35,6 +41,7 @@ __host__ __device__ constexpr int col_tc(int L) {
 // Column passes (pencil length L = 2 n, strided rows).  LDS = L * TC * sizeof(cx<T>).
 template <typename T>
 __host__ __device__ constexpr TileCfg col_cfg(int L, int v) {
+  constexpr bool d = sizeof(T) == 8;
   const int tc = col_tc<T>(L);
   // wider tiles (longer row segments, more LDS) for variant 2 of lengths 256-512;
   // the axis-0 pass never uses this shape (its variant 2 is the LDS-table or
@@ -42,19 +49,24 @@ __host__ __device__ constexpr TileCfg col_cfg(int L, int v) {
   const int tw = 2 * tc;
   switch (L) {
     case 16: return v == 0 ? TileCfg{0, tc, 1} : v == 1 ? TileCfg{1, tc, 4} : TileCfg{1, tc, 2};
-    case 24: return v == 0 ? TileCfg{0, tc, 1} : v == 1 ? TileCfg{1, tc, 2} : TileCfg{0, tc, 3};
+    case 24: return v == 0 ? TileCfg{1, tc, 2} : v == 1 ? TileCfg{0, tc, 1} : TileCfg{0, tc, 3};
     case 32: return v == 0 ? TileCfg{0, tc, 4} : v == 1 ? TileCfg{1, tc, 2} : TileCfg{0, tc, 8};
-    case 48: return v == 0 ? TileCfg{0, tc, 1} : v == 1 ? TileCfg{1, tc, 4} : TileCfg{0, tc, 3};
+    case 48: return v == 0 ? TileCfg{1, tc, 4} : v == 1 ? TileCfg{0, tc, 1} : TileCfg{0, tc, 3};
     case 64: return v == 0 ? TileCfg{0, tc, 8} : v == 1 ? TileCfg{1, tc, 4} : TileCfg{0, tc, 4};
-    case 96: return v == 0 ? TileCfg{0, tc, 4} : v == 1 ? TileCfg{1, tc, 4} : TileCfg{0, tc, 8};
+    case 96: return v == 0 ? TileCfg{1, tc, 4} : v == 1 ? TileCfg{0, tc, 4} : TileCfg{0, tc, 8};
     case 128: return v == 0 ? TileCfg{0, tc, 8} : v == 1 ? TileCfg{1, tc, 8} : TileCfg{0, tc, 16};
-    case 192: return v == 0 ? TileCfg{0, tc, 8} : v == 1 ? TileCfg{1, tc, 8} : TileCfg{0, tc, 16};
+    case 192: return v == 0 ? TileCfg{1, tc, 8} : v == 1 ? TileCfg{0, tc, 8} : TileCfg{0, tc, 16};
     case 256: return v == 0 ? TileCfg{0, tc, 16} : v == 1 ? TileCfg{1, tc, 32} : TileCfg{0, tw, 16};
-    case 384: return v == 0 ? TileCfg{0, tc, 8} : v == 1 ? TileCfg{1, tc, 16} : TileCfg{0, tw, 8};
-    case 512: return v == 0 ? TileCfg{0, tc, 16} : v == 1 ? TileCfg{1, tc, 32} : TileCfg{0, tw, 16};
+    case 384: return v == 0 ? TileCfg{1, tc, 16} : v == 1 ? TileCfg{0, tc, 8} : TileCfg{1, tw, 16};
+    case 512:
+      return v == (d ? 1 : 0)   ? TileCfg{0, tc, 16}
+             : v == (d ? 0 : 1) ? TileCfg{1, tc, 32}
+                                : TileCfg{0, tw, 16};
     // one block per compute unit at these lengths (L * TC complex of LDS): variant 2
-    // adds threads per pencil instead of columns
-    case 768: return v == 0 ? TileCfg{0, tc, 16} : v == 1 ? TileCfg{1, tc, 16} : TileCfg{0, tc, 32};
+    // adds threads per pencil instead of columns.  768 as 32 x 24: axis-0 pass at 384^3
+    // 1036 -> 620 us in float32, 2511 -> 1487 in float64 (the three-stage plan); the
+    // axis-1 passes 315 -> 279 and 353 -> 288
+    case 768: return v == 0 ? TileCfg{1, tc, 32} : v == 1 ? TileCfg{1, tc, 16} : TileCfg{0, tc, 32};
     case 1024: return v == 0 ? TileCfg{0, tc, 32} : v == 1 ? TileCfg{1, tc, 32} : TileCfg{1, tc, 64};
     default: return {0, 0, 0};
   }
@@ -66,43 +78,52 @@ __host__ __device__ constexpr TileCfg row_cfg(int LC, int v) {
   constexpr bool d = sizeof(T) == 8;
   switch (LC) {
     case 8: return v == 0 ? TileCfg{0, 64, 1} : v == 1 ? TileCfg{0, 32, 1} : TileCfg{0, 16, 1};
-    case 12: return v == 0 ? TileCfg{0, 64, 1} : v == 1 ? TileCfg{0, 32, 1} : TileCfg{0, 64, 3};
-    case 16: return v == 0 ? TileCfg{0, 64, 1} : v == 1 ? TileCfg{1, 32, 4} : TileCfg{1, 64, 2};
-    case 24: return v == 0 ? TileCfg{0, 64, 1} : v == 1 ? TileCfg{1, 32, 2} : TileCfg{0, 32, 3};
+    case 12: return v == 0 ? TileCfg{0, 64, 3} : v == 1 ? TileCfg{0, 32, 1} : TileCfg{0, 64, 1};
+    case 16: return v == 0 ? TileCfg{1, 32, 4} : v == 1 ? TileCfg{0, 64, 1} : TileCfg{1, 64, 2};
+    case 24: return v == 0 ? TileCfg{0, 32, 3} : v == 1 ? TileCfg{1, 32, 2} : TileCfg{0, 64, 1};
     case 32: return v == 0 ? TileCfg{0, 32, 4} : v == 1 ? TileCfg{1, 32, 2} : TileCfg{0, 16, 8};
-    case 48: return v == 0 ? TileCfg{0, d ? 32 : 64, 1} : v == 1 ? TileCfg{1, 32, 4} : TileCfg{0, 32, 3};
+    case 48: return v == 0 ? TileCfg{1, 16, 12} : v == 1 ? TileCfg{1, 32, 4} : TileCfg{0, 32, 3};
     case 64: return v == 0 ? TileCfg{0, 32, 8} : v == 1 ? TileCfg{1, 32, 4} : TileCfg{0, 16, 8};
     // 96 and 128: a variant with 16 threads a row, 128-byte row segments per wave
-    case 96: return v == 0 ? TileCfg{0, 32, 4} : v == 1 ? TileCfg{0, 8, 16} : TileCfg{0, 16, 8};
+    case 96: return v == 0 ? TileCfg{0, 8, 16} : v == 1 ? TileCfg{1, 8, 12} : TileCfg{0, 16, 8};
     case 128: return v == 0 ? TileCfg{0, d ? 8 : 16, 8} : v == 1 ? TileCfg{1, 16, 8} : TileCfg{1, 8, 16};
-    case 192: return v == 0 ? TileCfg{0, d ? 8 : 16, 8} : v == 1 ? TileCfg{1, 16, 8} : TileCfg{0, 8, 16};
+    case 192: return v == 0 ? TileCfg{0, 8, d ? 24 : 16} : v == 1 ? TileCfg{1, 16, 8} : TileCfg{0, 8, d ? 16 : 24};
     // 256 in float32: small blocks of 4 rows, 2-4 groups each (more bytes in flight a thread)
     case 256:
       return d ? (v == 0 ? TileCfg{0, 8, 16} : v == 1 ? TileCfg{1, 8, 32} : TileCfg{1, 4, 32, 2})
                : (v == 0 ? TileCfg{0, 4, 16, 4} : v == 1 ? TileCfg{1, 4, 32, 2} : TileCfg{0, 4, 16, 2});
-    case 384: return v == 0 ? TileCfg{0, d ? 4 : 8, 8} : v == 1 ? TileCfg{1, 8, 8} : TileCfg{0, 4, 16};
+    case 384: return v == 0 ? TileCfg{1, 8, 24} : v == 1 ? TileCfg{0, 4, 16} : TileCfg{0, 4, 24};
     // 512: the three-stage plan; 64 threads per row over 4 rows keeps 8 waves per SIMD
     case 512: return v == 0 ? TileCfg{1, 4, 64} : v == 1 ? TileCfg{1, 8, 32} : TileCfg{1, 16, 32};
     default: return {0, 0, 0};
   }
 }
 
-// Axis-0 pass variants: variant 0 as col_cfg, variant 1 as col_cfg or the
-// split-exchange form (conv_split_wpe, below); variant 2 keeps the
+// Axis-0 pass variants: variants 0 and 1 as conv_shape, variant 0 in the
+// split-exchange form where there is one (conv_split_wpe, below; variant 1 is
+// then the plain form of the same shape); variant 2 keeps the
 // complete twiddle table in LDS, with the shape of variant 0 (else 1) when the
 // table costs no resident block (conv_twf_fits) or saves registers
-// (conv_twf_wide), and with the split exchanges too where variant 1 has them;
+// (conv_twf_wide), and with the split exchanges too where variant 0 has them;
 // else it is the pipelined persistent kernel (grid of at most
-// CONV_PIPE_BLOCKS blocks) with the shape of variant 1.
+// CONV_PIPE_BLOCKS blocks) with the two-stage shape (conv_pipe_shape).
 constexpr int CONV_PIPE_BLOCKS = 1024;
 constexpr int CONV_GATHER_MIN_BLOCKS = 2048;
 constexpr int CONV_LDS_PER_CU = 163840;
+
+// Shape of the axis-0 pass's variants 0 and 1: col_cfg's, in the other order for
+// float64 pencils of 512 (16 threads a pencil 294-299 us at 256^3, 32 325; the
+// axis-1 passes gain from 32: 144 -> 141 and 149 -> 137).
+template <typename T>
+__host__ __device__ constexpr TileCfg conv_shape(int L, int v) {
+  return col_cfg<T>(L, sizeof(T) == 8 && L == 512 && v < 2 ? 1 - v : v);
+}
 
 // The table may not cost a resident block: as many blocks of the variant fit
 // in a compute unit's LDS with it as without it.
 template <typename T>
 __host__ __device__ constexpr bool conv_twf_fits(int L, int v) {
-  const TileCfg c = col_cfg<T>(L, v);
+  const TileCfg c = conv_shape<T>(L, v);
   const int base = L * c.tiles * 2 * (int)sizeof(T);
   const int with = base + twf_size(L, c.pid) * 2 * (int)sizeof(T);
   return plan_len(L, c.pid) > 1 && with <= CONV_LDS_PER_CU && CONV_LDS_PER_CU / with == CONV_LDS_PER_CU / base;
@@ -124,14 +145,15 @@ __host__ __device__ constexpr bool conv_twf(int L, int v) {
 
 template <typename T>
 __host__ __device__ constexpr bool conv_pipelined(int L, int v) {
-  return v == 2 && !conv_twf<T>(L, v) && L >= 128 && plan_len(L, col_cfg<T>(L, 1).pid) > 1;
+  return v == 2 && !conv_twf<T>(L, v) && L >= 128 && plan_len(L, conv_shape<T>(L, 1).pid) > 1;
 }
+// Its shape: variant 1's, but the two-stage plan where that is variant 0's.
+__host__ __device__ constexpr int conv_pipe_shape(int L) { return L == 192 || L == 384 ? 0 : 1; }
 
-// Axis-0 pass variant 1 where conv_split_wpe(L) > 0: the shape of variant 0
-// (a two-stage plan) with the exchange between its stages made through a real
+// Axis-0 pass variant 0 where conv_split_wpe(L) > 0: a two-stage plan with the exchange between its stages made through a real
 // LDS array in two rounds, real parts then imaginary parts (half the LDS of a
 // block), and the kernel built for that many waves per SIMD, so that more
-// blocks share a compute unit.  Elsewhere variant 1 is col_cfg's.
+// blocks share a compute unit (256^3 float32: 143 us against 150 plain).
 template <typename T>
 __host__ __device__ constexpr int conv_split_wpe(int L) {
   return sizeof(T) == 4 && L == 512 ? 3 : 0;
@@ -139,10 +161,10 @@ __host__ __device__ constexpr int conv_split_wpe(int L) {
 
 template <typename T>
 __host__ __device__ constexpr TileCfg conv_cfg(int L, int v) {
-  return conv_twf<T>(L, v) ? col_cfg<T>(L, conv_twf_fits<T>(L, 0) || conv_twf_wide<T>(L) ? 0 : 1)
-         : conv_pipelined<T>(L, v)                ? col_cfg<T>(L, 1)
-         : v == 1 && conv_split_wpe<T>(L) > 0     ? col_cfg<T>(L, 0)
-                                                  : col_cfg<T>(L, v);
+  return conv_twf<T>(L, v) ? conv_shape<T>(L, conv_twf_fits<T>(L, 0) || conv_twf_wide<T>(L) ? 0 : 1)
+         : conv_pipelined<T>(L, v)                ? conv_shape<T>(L, conv_pipe_shape(L))
+         : v == 1 && conv_split_wpe<T>(L) > 0     ? conv_shape<T>(L, 0)
+                                                  : conv_shape<T>(L, v);
 }
 
 #define FSP_ROW_LENGTHS(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512)
@@ -204,7 +226,7 @@ __host__ __device__ constexpr TileCfg grad_cfg(int L, int v) {
   // radix-24 stage has only 16)
   if (v == 0 && L >= 256 && L <= 512) return {L == 384 ? 0 : 1, tc, 1024 / tc < L / 8 ? 1024 / tc : L / 8};
   if (v == 0 && L > 512) return {1, tc, 512 / tc};
-  return col_cfg<T>(L, v == 2 ? 0 : v);
+  return conv_shape<T>(L, v == 2 ? 0 : v);
 }
 
 template <typename T>
@@ -270,7 +292,7 @@ hipError_t launch_col(int L, int v, int kind, const ColArgs& a, int items, hipSt
         else if constexpr (conv_twf<T>(LV, VV))                                                     \
           hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, true>), gridc,             \
                              dim3(cc.tiles * cc.nq), 0, s, b);                                      \
-        else if constexpr (VV == 1 && conv_split_wpe<T>(LV) > 0)                                    \
+        else if constexpr (VV == 0 && conv_split_wpe<T>(LV) > 0)                                    \
           hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, false, 0, true,            \
                                          conv_split_wpe<T>(LV)>),                                   \
                              gridc, dim3(cc.tiles * cc.nq), 0, s, b);                               \
