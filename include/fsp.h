@@ -168,8 +168,8 @@ fsp_status fsp_precompute(fsp_plan p, void* stream);
  * the plan's precision): Section 2.2 steps 1, 2, 4 and 5 (zero-pad, transform,
  * multiply by the transform of G2, inverse transform, restrict), the sum of
  * eq. (2) over the grid.  phi may equal rho (in place; Section 3.3 reuses the
- * rho field for phi).  Asynchronous on `stream`; enqueues five kernels and
- * allocates nothing.  FSP_ERR_NOT_READY before bind + precompute. */
+ * rho field for phi).  Asynchronous on `stream`; enqueues at most five
+ * kernels and allocates nothing.  FSP_ERR_NOT_READY before bind + precompute. */
 fsp_status fsp_solve(fsp_plan p, const void* rho, void* phi, void* stream);
 
 /* The five passes of fsp_solve (Section 2.2 steps 4-5 split by axis) run one

@@ -364,6 +364,12 @@ struct TuneKey {
 std::mutex g_tune_mu;
 std::map<TuneKey, std::array<int, 11>> g_tuned;  // schedule, the gradient's axis-0 variant, separate variants
 
+bool tiny_supported(const fsp_plan_s* p) {
+  if (p->chunks != 1) return false;
+  return p->d.prec == FSP_F64 ? fsp::tiny_supported<double>(p->n[0], p->n[1], p->n[2])
+                              : fsp::tiny_supported<float>(p->n[0], p->n[1], p->n[2]);
+}
+
 double model_bytes(const fsp_plan_s* p) {
   // P1 reads rho, writes (n2+1) n1 n0 complex; P2 reads that, writes 2 n1 (n2+1) n0;
   // P3 reads/writes 2 n1 (n2+1) n0 and reads the octant; P4 mirrors P2, P5 mirrors P1.
@@ -374,6 +380,8 @@ double model_bytes(const fsp_plan_s* p) {
   const double half1 = n0 * n1 * (n2 + 1) * 2;      // reals in (n2+1) n1 n0 complex
   const double half2 = n0 * 2 * n1 * (n2 + 1) * 2;  // reals in 2 n1 (n2+1) n0 complex
   const double octant = (n0 + 1) * (n1 + 1) * (n2 + 1);
+  if (tiny_supported(p) && std::all_of(p->var, p->var + 5, [](int v) { return v == 0; }))
+    return (2 * real_grid + octant) * s;  // one launch, S in LDS
   if (p->var[1] == fsp::FUSED) return (2 * real_grid + 4 * half1 + octant) * s;
   const double fwd = p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
   const double inv = p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
@@ -919,6 +927,7 @@ static fsp::SolveGeom group_geom(const fsp_plan_s* p, const int* var) {
   g.tw_c1[1] = gb + p->tw_c1_off[pc2];
   g.tw_c1[3] = gb + p->tw_c1_off[pc4];
   g.tw_c0 = gb + p->tw_c0_off[pc3];
+  g.split = gb + p->tw_row_off[0] + (size_t)fsp::tw_size(p->n[2], 0) * 2 * p->rb;
   return g;
 }
 
@@ -1277,15 +1286,21 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
       return r;
     };
     const int P = fsp::PLANE, Fu = fsp::FUSED;
-    const int cand[5][5] = {{best[0], best[1], best[2], best[3], best[4]},
+    const int cand[6][5] = {{best[0], best[1], best[2], best[3], best[4]},
                             {best[0], Fu, Fu, Fu, best[4]},
                             {P, P, best[2], P, P},
                             {P, P, best[2], best[3], best[4]},
-                            {best[0], best[1], best[2], P, P}};
-    const bool ok[5] = {true, fused_supported(p), plane_supported(p), plane_supported(p), plane_supported(p)};
-    float t[5] = {0, 0, 0, 0, 0};
+                            {best[0], best[1], best[2], P, P},
+                            {0, 0, 0, 0, 0}};  // tiny grids: the whole solve in one launch
+    const bool ok[6] = {true,
+                        fused_supported(p),
+                        plane_supported(p),
+                        plane_supported(p),
+                        plane_supported(p),
+                        tiny_supported(p) && std::any_of(best, best + 5, [](int v) { return v != 0; })};
+    float t[6] = {0, 0, 0, 0, 0, 0};
     int pick = 0;
-    for (int c = 0; c < 5 && e == hipSuccess; ++c) {
+    for (int c = 0; c < 6 && e == hipSuccess; ++c) {
       if (!ok[c]) continue;
       e = time_solve(cand[c], &t[c]);
       if (st_sched != FSP_OK) {
@@ -1420,11 +1435,12 @@ fsp_status fsp_autotune_batch(int count, const fsp_plan* plans, const void* cons
       *out = median_ms(rep_ms, reps);
     };
     const int P = fsp::PLANE;
+    const bool tiny = tiny_supported(p0);  // whole solves in one launch; such grids have no plane kernels
     const int cand[4][5] = {{sp[0], sp[1], base[2], sp[3], sp[4]},
-                            {P, P, base[2], sp[3], sp[4]},
+                            {tiny ? 0 : P, tiny ? 0 : P, tiny ? 0 : base[2], tiny ? 0 : sp[3], tiny ? 0 : sp[4]},
                             {sp[0], sp[1], base[2], P, P},
                             {P, P, base[2], P, P}};
-    const int ncand = plane_supported(p0) ? 4 : 1;
+    const int ncand = plane_supported(p0) ? 4 : tiny ? 2 : 1;
     float best_ms = 1e30f;
     int cur[5] = {cand[0][0], cand[0][1], cand[0][2], cand[0][3], cand[0][4]};
     bool timed = false;
