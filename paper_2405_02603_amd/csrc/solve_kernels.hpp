@@ -65,6 +65,7 @@ struct ColArgs {
   int n1;                     // P3: n1 (pairs k1 and 2 n1 - k1 share a Green's row)
   long long g_k1_stride;      // P3: reals between Green's blocks k1 (tiles (n0+1) TC)
   int stream;                 // StreamBits
+  int single;                 // P3: one pencil set a block; nouter counts all 2 n1 rows k1
   int ntail;                  // P3: leading blocks that gather column ncols - 1 over TC k1 pairs
   int gather_min;             // P3 (host side): grid size from which the launcher gathers
   // P3 with several outputs from one item (the gradient solve; nout == 0 otherwise)
@@ -347,6 +348,9 @@ __global__ __launch_bounds__(TC* NQ, WPE) void k_col_conv(ColArgs a) {
     col = a.col0 + tile * TC + c;
     cok = col < a.ncols;
   }
+  const bool single = !GRAD && a.single;
+  const int k1 = p;  // row of the first set; p is folded to its Green's row
+  if (single && p > a.n1) p = 2 * a.n1 - p;
   const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.tw);
   const unsigned rs = (unsigned)a.row_stride;  // row offsets of one pencil fit in 32 bits (unsigned: no sign extension)
   auto idx = [c](int row) { return row * TC + c; };
@@ -399,13 +403,14 @@ __global__ __launch_bounds__(TC* NQ, WPE) void k_col_conv(ColArgs a) {
   T gn[GPRE ? Lf::J : 1][GPRE ? Lf::R : 1];
 
   // k1 = p and its partner 2 n1 - p share the Green's rows; p = 0 and p = n1
-  // have no partner.  `second` (a second pencil set follows, with barriers) is
-  // block-uniform: gathered blocks always run it, and in the others p is the
-  // block's own; `two` is the per-lane load/store mask of that set.
-  const bool paired = !(p == 0 || p == a.n1);
+  // have no partner, and with `single` it is another block's first set.
+  // `second` (a second pencil set follows, with barriers) is block-uniform:
+  // gathered blocks always run it, and in the others p is the block's own;
+  // `two` is the per-lane load/store mask of that set.
+  const bool paired = !single && !(p == 0 || p == a.n1);
   const bool second = gathered || paired;
   const bool two = cok && paired;
-  const long long off_a = (long long)p * a.outer_stride + col;
+  const long long off_a = (long long)k1 * a.outer_stride + col;
   const long long off_b = (long long)(2 * a.n1 - p) * a.outer_stride + col;
   cx<T>* const data = reinterpret_cast<cx<T>*>(item_work(a));
   // The derivative tables are odd along their axis: their transform is -i T with

@@ -253,6 +253,24 @@ inline ColArgs conv_gather(const ColArgs& a, int tc) {
   return b;
 }
 
+// A block's two pencil sets (k1 and 2 n1 - k1) run one after the other, which
+// halves the reads of the octant; on a grid of fewer than CONV_SINGLE_BLOCKS
+// blocks (four a CU) that chain is what the pass waits for, and each set gets
+// a block of its own.  Whole solves, paired / single: 48^3 f64 28.8 / 27.3 us,
+// 64^3 f64 36.9 / 34.0, 64^3 f32 27.6 / 25.1, 96^3 f64 61.2 / 59.6, 96^3 f32 40.4 / 39.3, 256x64x64
+// f32 48.2 / 45.5; on larger launches it loses: 48x192x96 f64 (1261 blocks)
+// 56.3 / 57.1, nineteen 32^3 f32 in a batch (1254) 39.9 / 41.5, six 96^3 f32
+// (2328) 133.8 / 138.3.  Grids whose lone column is gathered are larger still.
+constexpr long long CONV_SINGLE_BLOCKS = 1024;
+inline ColArgs conv_single(const ColArgs& a, int items) {
+  ColArgs b = a;
+  if (b.ntail == 0 && (long long)b.nouter * b.ntiles * items < CONV_SINGLE_BLOCKS) {
+    b.single = 1;
+    b.nouter = 2 * b.n1;
+  }
+  return b;
+}
+
 // kind: 0 forward (P2), 1 inverse (P4), 2 forward-multiply-inverse (P3)
 template <typename T>
 hipError_t launch_col(int L, int v, int kind, const ColArgs& a, int items, hipStream_t s) {
@@ -284,7 +302,7 @@ hipError_t launch_col(int L, int v, int kind, const ColArgs& a, int items, hipSt
         hipLaunchKernelGGL((k_col_conv_pipe<T, LV, cc.pid, cc.tiles, cc.nq>), dim3(nb, items),      \
                            dim3(cc.tiles * cc.nq), 0, s, b);                                        \
       } else {                                                                                      \
-        const ColArgs b = conv_gather(a, cc.tiles);                                                 \
+        const ColArgs b = conv_single(conv_gather(a, cc.tiles), items);                             \
         const dim3 gridc((unsigned)(b.nouter * b.ntiles + b.ntail), (unsigned)items);               \
         if constexpr (conv_twf<T>(LV, VV) && conv_split_wpe<T>(LV) > 0)                            \
           hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, true, 0, true,             \
