@@ -221,8 +221,12 @@ fsp_status fsp_solve_grad(fsp_plan p, const void* rho, void* phi, void* grad, vo
  * fsp_solve_passes then accepts only ranges that contain both passes of such
  * a pair or neither (FSP_ERR_INVALID_ARG otherwise).  The plane pairs and the
  * fused schedule exclude each other.
- * Results are identical up to rounding order across schedules.  A new plan starts with the schedule last tuned for its grid and
- * precision in this process (else all zeros). */
+ * All zeros let the library pick: whole solves and gradients on grids with
+ * n1 == n2 in {32, 48, 64} then run both plane pairs, which are the faster
+ * there for any number of solves; passes asked for one by one stay separate.
+ * Results are identical up to rounding order across schedules.  A new plan starts
+ * with the schedule last tuned for its grid and precision in this process (else
+ * all zeros). */
 fsp_status fsp_plan_get_schedule(fsp_plan p, int* variants /* [5] */);
 fsp_status fsp_plan_set_schedule(fsp_plan p, const int* variants /* [5] */);
 
@@ -238,7 +242,8 @@ fsp_status fsp_plan_set_schedule(fsp_plan p, const int* variants /* [5] */);
  * `stream`.  times_ms (NULL or [5 * 3 + 5]) receives the median time of each
  * variant, times_ms[pass * 3 + variant], then the median time of whole solves
  * with schedules built from the best variants: times_ms[15] passes 1-3 fused,
- * [16] all passes separate, [17] both plane pairs (0-1 and 3-4), [18] the
+ * [16] the fastest variant of each pass (separate passes, unless all are 0 and
+ * that schedule picks other kernels), [17] both plane pairs (0-1 and 3-4), [18] the
  * plane pair 0-1 alone, [19] the pair 3-4 alone (0 where the schedule is not
  * supported); the fastest of these schedules is kept.  On a plan with
  * FSP_WANT_GRAD it also times the gradient solve's axis-0 pass (four outputs)

@@ -370,6 +370,19 @@ bool tiny_supported(const fsp_plan_s* p) {
                               : fsp::tiny_supported<float>(p->n[0], p->n[1], p->n[2]);
 }
 
+// Whole solves, and gradients, on the default variants (all 0) run passes 0-1
+// and 3-4 as plane kernels at 32, 48 and 64 points, whose planes are one column
+// tile.  There the pairs were the faster, or equal, at every count measured
+// (separate / planes): one solve of 32^3 f32 23.5 / 15.7 us, 48^3 23.6 / 20.4,
+// 64^3 26.7 / 23.6, f64 22.4 / 15.7, 25.0 / 25.1, 34.2 / 29.9; 128 solves f32
+// 143 / 94, 385 / 324, 865 / 702, f64 195 / 151, 670 / 565, 732 (64 solves) / 609;
+// gradients 28.5 / 24.0, 43.2 / 38.5, 44.3 / 38.1.  At 96 they are not (41.8 / 54).
+bool default_planes(const fsp_plan_s* p) {
+  if (p->n[1] != p->n[2] || p->chunks != 1) return false;
+  if (std::any_of(p->var, p->var + 5, [](int v) { return v != 0; })) return false;
+  return p->d.prec == FSP_F64 ? fsp::plane_default<double>(p->n[2]) : fsp::plane_default<float>(p->n[2]);
+}
+
 double model_bytes(const fsp_plan_s* p) {
   // P1 reads rho, writes (n2+1) n1 n0 complex; P2 reads that, writes 2 n1 (n2+1) n0;
   // P3 reads/writes 2 n1 (n2+1) n0 and reads the octant; P4 mirrors P2, P5 mirrors P1.
@@ -383,8 +396,9 @@ double model_bytes(const fsp_plan_s* p) {
   if (tiny_supported(p) && std::all_of(p->var, p->var + 5, [](int v) { return v == 0; }))
     return (2 * real_grid + octant) * s;  // one launch, S in LDS
   if (p->var[1] == fsp::FUSED) return (2 * real_grid + 4 * half1 + octant) * s;
-  const double fwd = p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
-  const double inv = p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  const bool planes = default_planes(p);
+  const double fwd = planes || p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  const double inv = planes || p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
   return (fwd + 2 * half2 + octant + inv) * s;
 }
 
@@ -892,7 +906,15 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
 
 // Shape fields shared by every item of a launch group (items filled by the caller).
 static fsp::SolveGeom group_geom(const fsp_plan_s* p, const int* var);
-static fsp::SolveGeom group_geom(const fsp_plan_s* p) { return group_geom(p, p->var); }
+
+// Shape fields for passes first..last of the plan's schedule: whole solves on
+// the default variants take the plane kernels where those are the faster for
+// every number of items (default_planes).
+static fsp::SolveGeom group_geom(const fsp_plan_s* p, int first = 0, int last = 4) {
+  constexpr int P = fsp::PLANE;
+  constexpr int planes[5] = {P, P, 0, P, P};
+  return group_geom(p, first == 0 && last == 4 && default_planes(p) ? planes : p->var);
+}
 
 // Shape fields with an explicit schedule.
 static fsp::SolveGeom group_geom(const fsp_plan_s* p, const int* var) {
@@ -958,7 +980,7 @@ static hipError_t run_group(const fsp::SolveGeom& g, bool f64, int first, int la
 }
 
 static fsp_status solve_one(fsp_plan p, const void* rho, void* phi, hipStream_t s, int first = 0, int last = 4) {
-  fsp::SolveGeom g = group_geom(p);
+  fsp::SolveGeom g = group_geom(p, first, last);
   add_item(g, p, rho, phi);
   hipError_t e = run_group(g, p->d.prec == FSP_F64, first, last, s);
   if (e != hipSuccess) return fail_hip(e, "fsp_solve");
@@ -1114,6 +1136,7 @@ static fsp::SolveGeom grad_geom(const fsp_plan_s* p, const void* rho, void* phi,
   int var[5];
   for (int i = 0; i < 5; ++i) var[i] = p->var[i];
   if (var[1] == fsp::FUSED) var[1] = var[2] = var[3] = 0;
+  if (default_planes(p)) var[0] = var[1] = var[3] = var[4] = fsp::PLANE;
   if (p3 >= 0) var[2] = p3;
   fsp::SolveGeom g = group_geom(p, var);
   const int gp = p->d.prec == FSP_F64 ? fsp::grad_cfg<double>(2 * p->n[0], var[2]).pid

@@ -21,16 +21,24 @@
 //                transform of length 2 n2, first n2 samples kept, as in P5, to
 //                phi.
 //
-// The block's LDS is the plane alone (rows at the row passes' padded pitch),
-// so more blocks share a compute unit.  Rows and columns are transformed with
+// The block's LDS is the plane alone (rows at the row passes' padded pitch)
+// and a strip, so more blocks share a compute unit.  Rows and columns are transformed with
 // the same length-n plan and twiddle table (n1 == n2), whose split table
 // exp(-i pi k / n2) also gives the w^i above.  Row phase: NQR threads per row,
 // NT / NQR rows at a time.  Column phase: TC adjacent columns (consecutive
-// lanes, contiguous in S) with NQC threads per pencil, n2 / TC full column
-// tiles and one tile for the column k = n2 alone; that tile's other lanes
-// transform a column that holds no live data at that point (one already
-// stored by the forward kernel, one yet to be filled by the inverse kernel)
-// and store nothing.
+// lanes, contiguous in S) with NQC threads per pencil, n2 / TC tiles.  The
+// columns k = 0 and k = n2 of a real plane are real: they share the plane's
+// column 0 as A + i B and one transform, told apart by its symmetry when the
+// forward kernel stores them and by real and imaginary part in the rows of the
+// inverse one.  Before, the column n2 was a tile of its own, most of whose lanes
+// did nothing: sixty-four 48^3 solves float32 163 -> 151 us with the planes,
+// thirty-two of 64^3 172 -> 167, eight of 128^3 381 -> 355, 64^3 alone 30.9 -> 26.
+//
+// What bounds them: many planes, memory (S is written and read once); few, the
+// chain of stages inside a block, of which a compute unit then holds only one
+// or two.  So where a plane is small all columns are one tile (eight waves a
+// block at n = 64) and the inverse kernel's two half-length transforms run side
+// by side in two planes (PAIR).
 #pragma once
 
 #include "solve_kernels.hpp"
@@ -62,26 +70,47 @@ template <typename T>
 __host__ __device__ constexpr PlaneCfg plane_cfg(int N) {
   if constexpr (sizeof(T) == 4) {
     switch (N) {
-      case 32: return {0, 4, 32, 4, 2};
+      case 32: return {0, 8, 32, 8, 1};
       case 48: return {1, 4, 16, 12, 4};
-      case 64: return {0, 4, 32, 8, 4};
+      case 64: return {0, 8, 64, 8, 1};
       case 96: return {0, 16, 32, 16, 4};
       case 128: return {1, 4, 32, 16, 2};
       default: return {0, 0, 0, 0, 0};
     }
   } else {
     switch (N) {
-      case 32: return {0, 4, 32, 4, 2};
+      case 32: return {0, 8, 32, 8, 1};
       case 48: return {1, 4, 16, 12, 2};
-      case 64: return {0, 4, 16, 8, 1};
+      case 64: return {0, 8, 64, 8, 1};
       default: return {0, 0, 0, 0, 0};
     }
   }
 }
 
+// Planes of a launch up to which 48 points take their own wide shape: two a
+// compute unit.  Whole solves, {1, 4, 16, 12} / wide: 48 planes f32 29.0 / 25.1
+// us, 384 40.7 / 37.1, 576 49.6 / 51.5, 3072 150 / 170.  At 32 and 64 points the
+// wide shape is the faster throughout, or equal, and the only one: 64 planes of
+// 64 x 64 f32 29.7 / 27.3 ({0, 4, 32, 8} / wide), 512 59.5 / 55.9, 8192 753 /
+// 745, f64 64 43.3 / 34.4, 1024 153.6 / 148.1, 8192 641 / 650.
+constexpr int PLANE_FEW = 512;
 template <typename T>
-__host__ __device__ constexpr int plane_lds_bytes(int N) {
-  return N * row_pitch(N) * 2 * (int)sizeof(T);
+__host__ __device__ constexpr PlaneCfg plane_few_cfg(int N) {
+  return N == 48 ? PlaneCfg{1, 12, 48, 12, 1} : plane_cfg<T>(N);
+}
+
+// One column tile: the inverse kernel takes two planes of LDS, and whole solves
+// on the default variants run as plane kernels.
+__host__ __device__ constexpr bool plane_wide(int N, const PlaneCfg& c) { return c.tc == N; }
+template <typename T>
+__host__ __device__ constexpr bool plane_default(int N) {
+  return plane_cfg<T>(N).tc > 0 && plane_wide(N, plane_few_cfg<T>(N));
+}
+
+template <typename T>
+__host__ __device__ constexpr int plane_lds_bytes(int N, const PlaneCfg& c) {
+  const int fwd = N * row_pitch(N) + 2 * N, inv = (plane_wide(N, c) ? 2 : 1) * N * row_pitch(N);
+  return (fwd > inv ? fwd : inv) * 2 * (int)sizeof(T);
 }
 
 // One length-N transform of the pencils of a column tile, in place in the
@@ -107,6 +136,7 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
   constexpr int K = plan_len(LC, PID);
   static_assert(K > 1, "the column transforms exchange through the plane");
   __shared__ cx<T> pl[N * PP];
+  __shared__ cx<T> two[2][N];  // the packed column's transform, even and odd outputs
   const int tid = threadIdx.x;
   const int i0 = blockIdx.x;
   const cx<T>* rho = reinterpret_cast<const cx<T>*>(a.items ? table_item(a.items, blockIdx.y).rho : a.in[blockIdx.y]);
@@ -119,19 +149,23 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
   using F = FirstStage<LC, PID, false, NQR>;
   static_assert(F::R % 2 == 0, "forward plans start with an even radix");
   cx<T> raw[G][F::J][F::R / 2];
+  // rho is read once, but its lines pay as cached ones until S itself leaves the
+  // caches (sixty-four 48^3 float32 160 -> 151 us; 128 of 64^3 724 against 750)
+  by_stream(a.stream & STREAM_COL_STORE, [&](auto sm) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const int i1 = g * TRR + cr;
-    const cx<T>* in = rho + ((long long)i0 * N + i1) * (LC / 2);
-    issue_fence();
+    for (int g = 0; g < G; ++g) {
+      const int i1 = g * TRR + cr;
+      const cx<T>* in = rho + ((long long)i0 * N + i1) * (LC / 2);
+      issue_fence();
 #pragma unroll
-    for (int j = 0; j < F::J; ++j) {
-      const int b = qr + NQR * j;
-      const bool ok = (F::NB % NQR == 0) || b < F::NB;
+      for (int j = 0; j < F::J; ++j) {
+        const int b = qr + NQR * j;
+        const bool ok = (F::NB % NQR == 0) || b < F::NB;
 #pragma unroll
-      for (int r = 0; r < F::R / 2; ++r) raw[g][j][r] = ok ? ld_once(&in[b + r * F::NB]) : czero<T>();
+        for (int r = 0; r < F::R / 2; ++r) raw[g][j][r] = ok ? ld_as<sm.value>(&in[b + r * F::NB]) : czero<T>();
+      }
     }
-  }
+  });
   issue_fence();
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -162,7 +196,7 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
     lds_barrier();
     // split: the n2 + 1 non-negative frequencies of the real row, in place.  A
     // thread takes k and n2 - k together (k <= n2 / 2): it alone reads and
-    // writes those two slots (k == 0 pairs with the slot n2, from z_0 alone).
+    // writes those two slots (k == 0: X[0] and X[n2], both real, packed).
     constexpr int JS = (LC / 2 + 1 + NQR - 1) / NQR;
 #pragma unroll
     for (int j = 0; j < JS; ++j) {
@@ -170,6 +204,7 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
       if (k <= LC / 2) {
         const cx<T> Za = pl[idx(k)];
         const cx<T> Zb = pl[idx(k == 0 ? 0 : LC - k)];
+        const bool packed = k == 0;
         auto split = [](cx<T> A, cx<T> Bc, cx<T> t) {
           const cx<T> B = conjg(Bc);
           const cx<T> E = {T(0.5) * (A.x + B.x), T(0.5) * (A.y + B.y)};
@@ -179,27 +214,26 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
         };
         const cx<T> Xa = split(Za, Zb, pp[k]);       // X[k]
         const cx<T> Xb = split(Zb, Za, pp[LC - k]);  // X[n2 - k]
-        pl[idx(k)] = Xa;
-        if (k != LC / 2) pl[idx(LC - k)] = Xb;
+        pl[idx(k)] = packed ? cx<T>{Za.x + Za.y, Za.x - Za.y} : Xa;
+        if (!packed && k != LC / 2) pl[idx(LC - k)] = Xb;
       }
     }
   }
   lds_barrier();
 
-  // ---- columns k <= n2: even and odd outputs of the axis-1 forward transform
+  // ---- columns k < n2: even and odd outputs of the axis-1 forward transform
   const int c = tid % TC, q = tid / TC;
   using FC = FirstStage<N, PID, false, NQC>;
   using LC_ = LastStage<N, PID, false, NQC>;
-  constexpr int NTILE = N / TC + 1;  // the last tile holds the column n2 alone
+  constexpr int NTILE = N / TC;
   cx<T>* const Sb = S + (long long)i0 * a.plane;
   const unsigned P = (unsigned)a.pitch;
 #pragma unroll 1
   for (int t = 0; t < NTILE; ++t) {
     const int k = t * TC + c;
-    const bool kok = k <= N;
-    const int ks = row_slot(kok ? k : c);  // past n2: a column of the first tile, already stored
+    const int ks = row_slot(k);
     auto cidx = [ks](int row) { return row * PP + ks; };
-    cx<T> ve[FC::J][FC::R], vo[FC::J][FC::R];
+    cx<T> v[2][FC::J][FC::R];  // inputs of the even and of the odd outputs
 #pragma unroll
     for (int j = 0; j < FC::J; ++j) {
       const int b = q + NQC * j;
@@ -207,43 +241,65 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_fwd(PlaneArgs a) {
 #pragma unroll
         for (int r = 0; r < FC::R; ++r) {
           const int i1 = b + r * FC::NB;
-          ve[j][r] = pl[cidx(i1)];
-          vo[j][r] = cmul(ve[j][r], pp[i1]);
+          v[0][j][r] = pl[cidx(i1)];
+          v[1][j][r] = cmul(v[0][j][r], pp[i1]);
         }
-        Dft<FC::R, false, T>::run(ve[j]);
-        Dft<FC::R, false, T>::run(vo[j]);
+        Dft<FC::R, false, T>::run(v[0][j]);
+        Dft<FC::R, false, T>::run(v[1][j]);
       }
     }
     lds_barrier();  // the column's inputs are in registers before the transforms overwrite it
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      if (half == 1) lds_barrier();  // the even transform's last stage has read the column
+    for (int h = 0; h < 2; ++h) {
+      if (h == 1) lds_barrier();  // the even transform's last stage has read the column
       cx<T> w[LC_::J][LC_::R];
-      plane_column_fft<T, N, PID, false, NQC>(pl, tw, q, cidx, half == 0 ? ve : vo, w);
+      plane_column_fft<T, N, PID, false, NQC>(pl, tw, q, cidx, v[h], w);
+      if (k == 0) {  // packed: unpacked below
+#pragma unroll
+        for (int j = 0; j < LC_::J; ++j) {
+          const int b = q + NQC * j;
+          if ((LC_::NB % NQC == 0) || b < LC_::NB) {
+#pragma unroll
+            for (int m = 0; m < LC_::R; ++m) two[h][b + m * LC_::NB] = w[j][m];
+          }
+        }
+      }
       by_stream(a.stream & STREAM_COL_STORE, [&](auto sm) {
 #pragma unroll
         for (int j = 0; j < LC_::J; ++j) {
           const int b = q + NQC * j;
-          if (kok && ((LC_::NB % NQC == 0) || b < LC_::NB)) {
+          if (k > 0 && ((LC_::NB % NQC == 0) || b < LC_::NB)) {
 #pragma unroll
             for (int m = 0; m < LC_::R; ++m)
-              put<sm.value>(&Sb[(2 * (b + m * LC_::NB) + half) * P + k], w[j][m]);
+              put<sm.value>(&Sb[(2 * (b + m * LC_::NB) + h) * P + k], w[j][m]);
           }
         }
       });
     }
-    lds_barrier();  // the next tile's lanes past n2 reuse columns of the first tile
   }
+  // C = A + i B of the two real columns k = 0 (A) and k = n2 (B): the outputs
+  // 2 m + h and 2 n1 - (2 m + h) of C give both columns' 2 m + h.
+  lds_barrier();
+  by_stream(a.stream & STREAM_COL_STORE, [&](auto sm) {
+    for (int e = tid; e < 2 * N; e += NT) {
+      const int h = e / N, m = e % N;
+      const cx<T> C = two[h][m], D = conjg(two[h][h ? N - 1 - m : m ? N - m : 0]);
+      cx<T>* const row = Sb + (long long)(2 * m + h) * P;
+      put<sm.value>(&row[0], cx<T>{T(0.5) * (C.x + D.x), T(0.5) * (C.y + D.y)});
+      put<sm.value>(&row[N], cx<T>{T(0.5) * (C.y - D.y), T(0.5) * (D.x - C.x)});
+    }
+  });
 }
 
-template <typename T, int N, int PID, int NQR, int TC, int NQC, int WPE>
+// PAIR: two planes of LDS, a column's two half-length transforms run side by side.
+template <typename T, int N, int PID, int NQR, int TC, int NQC, int WPE, bool PAIR = false>
 __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
   constexpr int LC = N, NT = TC * NQC, TRR = NT / NQR, G = N / TRR;
   static_assert(NT % NQR == 0 && N % TRR == 0 && N % TC == 0, "row groups and column tiles tile the plane");
   constexpr int PP = row_pitch(LC);
   constexpr int K = plan_len(LC, PID);
   static_assert(K > 1, "the column transforms exchange through the plane");
-  __shared__ cx<T> pl[N * PP];
+  __shared__ cx<T> pl[(PAIR ? 2 : 1) * N * PP];
   const int tid = threadIdx.x;
   const int i0 = blockIdx.x;
   const cx<T>* S = reinterpret_cast<const cx<T>*>(a.items ? table_item(a.items, blockIdx.y).work : a.in[blockIdx.y]);
@@ -251,24 +307,21 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
   const cx<T>* tw = reinterpret_cast<const cx<T>*>(a.twr);
   const cx<T>* pp = tw + tw_size(LC, PID);  // exp(-i pi k / n2)
 
-  // ---- columns k <= n2 of S plane i0: rows i < n1 of the axis-1 inverse transform
+  // ---- columns k < n2 of S plane i0: rows i < n1 of the axis-1 inverse transform
   const int c = tid % TC, q = tid / TC;
   using FC = FirstStage<N, PID, true, NQC>;
   using LC_ = LastStage<N, PID, true, NQC>;
-  constexpr int NTILE = N / TC + 1;  // the column n2 alone comes first
+  constexpr int NTILE = N / TC;
   const cx<T>* const Sb = S + (long long)i0 * a.plane;
   const unsigned P = (unsigned)a.pitch;
-  // tile t: the column n2 for t == 0, else columns (t - 1) TC + c
-  auto col_of = [c](int t) { return t == 0 ? N + c : (t - 1) * TC + c; };
   // even rows 2 m and odd rows 2 m + 1 of the next tile are requested before
   // the current tile is transformed
   auto load_tile = [&](int t, cx<T> (&e)[FC::J][FC::R], cx<T> (&o)[FC::J][FC::R]) {
-    const int k = col_of(t);
-    const bool kok = t < NTILE && k <= N;
+    const int k = t * TC + c;
 #pragma unroll
     for (int j = 0; j < FC::J; ++j) {
       const int b = q + NQC * j;
-      const bool ok = kok && ((FC::NB % NQC == 0) || b < FC::NB);
+      const bool ok = t < NTILE && ((FC::NB % NQC == 0) || b < FC::NB);
 #pragma unroll
       for (int r = 0; r < FC::R; ++r) {
         const unsigned row = 2 * (b + r * FC::NB);
@@ -278,14 +331,32 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
     }
   };
   cx<T> ne[FC::J][FC::R], no[FC::J][FC::R];
+  // column 0 carries the column n2: A + i B, both inverse transforms real
+  cx<T> be[FC::J][FC::R], bo[FC::J][FC::R];
   issue_fence();
+#pragma unroll
+  for (int j = 0; j < FC::J; ++j) {
+    const int b = q + NQC * j;
+    const bool ok = c == 0 && ((FC::NB % NQC == 0) || b < FC::NB);
+#pragma unroll
+    for (int r = 0; r < FC::R; ++r) {
+      const unsigned row = 2 * (b + r * FC::NB);
+      be[j][r] = ok ? ld(&Sb[row * P + N]) : czero<T>();
+      bo[j][r] = ok ? ld(&Sb[(row + 1) * P + N]) : czero<T>();
+    }
+  }
   load_tile(0, ne, no);
   issue_fence();
+#pragma unroll
+  for (int j = 0; j < FC::J; ++j)
+#pragma unroll
+    for (int r = 0; r < FC::R; ++r) {
+      ne[j][r] = {ne[j][r].x - be[j][r].y, ne[j][r].y + be[j][r].x};
+      no[j][r] = {no[j][r].x - bo[j][r].y, no[j][r].y + bo[j][r].x};
+    }
 #pragma unroll 1
   for (int t = 0; t < NTILE; ++t) {
-    const int k = col_of(t);
-    // past n2 (tile 0 only): a column of the first full tile, filled later
-    const int ks = row_slot(k <= N ? k : c);
+    const int ks = row_slot(t * TC + c);
     auto cidx = [ks](int row) { return row * PP + ks; };
     cx<T> ve[FC::J][FC::R], vo[FC::J][FC::R];
 #pragma unroll
@@ -301,9 +372,20 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
       Dft<FC::R, true, T>::run(vo[j]);
     }
     cx<T> ye[LC_::J][LC_::R], yo[LC_::J][LC_::R];
-    plane_column_fft<T, N, PID, true, NQC>(pl, tw, q, cidx, ve, ye);
-    lds_barrier();  // the even transform's last stage has read the column
-    plane_column_fft<T, N, PID, true, NQC>(pl, tw, q, cidx, vo, yo);
+    if constexpr (PAIR) {  // both transforms at once, the odd one in the second plane
+      cx<T>* const p2 = pl + N * PP;
+      write_first_outputs<T, FC::R, FC::J, FC::NB, NQC>(pl, ve, q, cidx);
+      write_first_outputs<T, FC::R, FC::J, FC::NB, NQC>(p2, vo, q, cidx);
+      lds_barrier();
+      lds_stages<T, N, PID, true, 1, K - 1, NQC, true>(pl, tw, q, cidx);
+      lds_stages<T, N, PID, true, 1, K - 1, NQC, true>(p2, tw, q, cidx);
+      lds_last_stage<T, N, PID, true, NQC, true>(pl, tw, q, cidx, ye);
+      lds_last_stage<T, N, PID, true, NQC, true>(p2, tw, q, cidx, yo);
+    } else {
+      plane_column_fft<T, N, PID, true, NQC>(pl, tw, q, cidx, ve, ye);
+      lds_barrier();  // the even transform's last stage has read the column
+      plane_column_fft<T, N, PID, true, NQC>(pl, tw, q, cidx, vo, yo);
+    }
     lds_barrier();  // the odd transform's last stage has read the column
 #pragma unroll
     for (int j = 0; j < LC_::J; ++j) {
@@ -316,8 +398,8 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
         }
       }
     }
-    lds_barrier();  // after tile 0, the next tile's columns may hold that tile's stray results
   }
+  lds_barrier();
 
   // ---- rows of the plane: inverse real transforms of length 2 n2, first n2 samples to phi
   const int qr = tid % NQR, cr = tid / NQR;
@@ -335,10 +417,10 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
         for (int r = 0; r < F::R; ++r) {
           const int n = b + r * F::NB;
           const cx<T> X1 = pl[idx(n)];
-          const cx<T> X2 = conjg(pl[idx(LC - n)]);
+          const cx<T> X2 = conjg(pl[idx(n == 0 ? 0 : LC - n)]);
           const cx<T> A = cadd(X1, X2);
           const cx<T> B = cmulc(csub(X1, X2), pp[n]);
-          v[j][r] = {A.x - B.y, A.y + B.x};
+          v[j][r] = n == 0 ? cx<T>{X1.x + X1.y, X1.x - X1.y} : cx<T>{A.x - B.y, A.y + B.x};
         }
         Dft<F::R, true, T>::run(v[j]);
       }
@@ -370,17 +452,28 @@ __global__ __launch_bounds__(TC* NQC, WPE) void k_plane_inv(PlaneArgs a) {
 template <typename T>
 hipError_t launch_plane(int N, int n0, bool inv, const PlaneArgs& a, int items, hipStream_t s) {
   bool found = false;
+  const long long planes = (long long)n0 * items;
 #define FSP_CASE(NV)                                                                                \
   if (N == NV) {                                                                                    \
-    constexpr PlaneCfg c = plane_cfg<T>(NV);                                                        \
+    constexpr PlaneCfg c = plane_cfg<T>(NV), w = plane_few_cfg<T>(NV);                              \
     if constexpr (c.tc > 0) {                                                                       \
-      static_assert(plane_lds_bytes<T>(NV) <= 163840, "the plane fits in LDS"); \
-      if (inv)                                                                                      \
-        hipLaunchKernelGGL((k_plane_inv<T, NV, c.pid, c.nqr, c.tc, c.nqc, c.wpe>), dim3(n0, items),         \
-                           dim3(c.tc * c.nqc), 0, s, a);                                            \
-      else                                                                                          \
-        hipLaunchKernelGGL((k_plane_fwd<T, NV, c.pid, c.nqr, c.tc, c.nqc, c.wpe>), dim3(n0, items),         \
-                           dim3(c.tc * c.nqc), 0, s, a);                                            \
+      static_assert(w.pid == c.pid, "both shapes read one twiddle table");                          \
+      static_assert(plane_lds_bytes<T>(NV, w) <= 163840 && plane_lds_bytes<T>(NV, c) <= 163840, "LDS"); \
+      constexpr bool cw = plane_wide(NV, c), ww = plane_wide(NV, w);                                \
+      if (planes > PLANE_FEW) {                                                                     \
+        if (inv)                                                                                    \
+          hipLaunchKernelGGL((k_plane_inv<T, NV, c.pid, c.nqr, c.tc, c.nqc, c.wpe, cw>),            \
+                             dim3(n0, items), dim3(c.tc * c.nqc), 0, s, a);                         \
+        else                                                                                        \
+          hipLaunchKernelGGL((k_plane_fwd<T, NV, c.pid, c.nqr, c.tc, c.nqc, c.wpe>),                \
+                             dim3(n0, items), dim3(c.tc * c.nqc), 0, s, a);                         \
+      } else if (inv) {                                                                             \
+        hipLaunchKernelGGL((k_plane_inv<T, NV, w.pid, w.nqr, w.tc, w.nqc, w.wpe, ww>),              \
+                           dim3(n0, items), dim3(w.tc * w.nqc), 0, s, a);                           \
+      } else {                                                                                      \
+        hipLaunchKernelGGL((k_plane_fwd<T, NV, w.pid, w.nqr, w.tc, w.nqc, w.wpe>),                  \
+                           dim3(n0, items), dim3(w.tc * w.nqc), 0, s, a);                           \
+      }                                                                                             \
       found = true;                                                                                 \
     }                                                                                               \
   }
