@@ -223,7 +223,8 @@ fsp_status fsp_solve_grad(fsp_plan p, const void* rho, void* phi, void* grad, vo
  * fused schedule exclude each other.
  * All zeros let the library pick: whole solves and gradients on grids with
  * n1 == n2 in {32, 48, 64} then run both plane pairs, which are the faster
- * there for any number of solves; passes asked for one by one stay separate.
+ * there for any number of solves, and whole solves whose spectrum fits in LDS
+ * (n0, n1 <= 16, n2 <= 32) one kernel; passes asked for one by one stay separate.
  * Results are identical up to rounding order across schedules.  A new plan starts
  * with the schedule last tuned for its grid and precision in this process (else
  * all zeros). */
@@ -354,7 +355,8 @@ fsp_status fsp_plan_octant_offset(fsp_plan p, int component, size_t* offset);
 
 /* Model bytes that one solve moves through HBM with this plan's schedule
  * (reads + writes of its kernels, the Green's octant included: five passes,
- * fewer where the fused slab or a plane pair keeps intermediates in LDS): the
+ * fewer where the fused slab or a plane pair of the schedule keeps intermediates
+ * in LDS; all zeros count as five passes): the
  * memory traffic against which Section 3.4 finds the solve memory-bound. */
 fsp_status fsp_plan_model_bytes(fsp_plan p, double* bytes);
 

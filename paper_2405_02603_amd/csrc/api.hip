@@ -388,17 +388,15 @@ double model_bytes(const fsp_plan_s* p) {
   // P3 reads/writes 2 n1 (n2+1) n0 and reads the octant; P4 mirrors P2, P5 mirrors P1.
   // The fused slab (passes 1-3) reads and writes the (n2+1) n1 n0 rows once; a
   // plane pair reads rho and writes S (0-1), or reads S and writes phi (3-4).
+  // All zeros count as the five passes, whichever kernels they run as.
   const double n0 = p->n[0], n1 = p->n[1], n2 = p->n[2], s = p->rb;
   const double real_grid = n0 * n1 * n2;
   const double half1 = n0 * n1 * (n2 + 1) * 2;      // reals in (n2+1) n1 n0 complex
   const double half2 = n0 * 2 * n1 * (n2 + 1) * 2;  // reals in 2 n1 (n2+1) n0 complex
   const double octant = (n0 + 1) * (n1 + 1) * (n2 + 1);
-  if (tiny_supported(p) && std::all_of(p->var, p->var + 5, [](int v) { return v == 0; }))
-    return (2 * real_grid + octant) * s;  // one launch, S in LDS
   if (p->var[1] == fsp::FUSED) return (2 * real_grid + 4 * half1 + octant) * s;
-  const bool planes = default_planes(p);
-  const double fwd = planes || p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
-  const double inv = planes || p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  const double fwd = p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  const double inv = p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
   return (fwd + 2 * half2 + octant + inv) * s;
 }
 
