@@ -34,18 +34,17 @@
 // then share out the rows, each holding its 16 x 16 accumulators, and read their
 // matrix operands straight into registers from an image in the operand layout
 // (it stays in the L2; a fill kernel writes it, so nothing is uploaded): no
-// barrier between the fill and the results.  n / 2 doubles a column and part
-// leave two blocks a compute unit up to n = 256.
+// barrier between the fill and the results.  16 columns of a long axis leave
+// two blocks or more a compute unit.
 //
-// Measured (kernel trace, 256^3 Vico-Greengard): samples and six contractions
-// before 3.82 ms, now 1.36 ms (axis 0 0.73, axis 1 0.38, axis 2 0.25); 128^3
-// 480 -> 134 us; Hockney-Eastwood 64^3 float64 55 -> 29 us.  What bounds it: the
+// Measured (256^3 Vico-Greengard): samples and six contractions before 3.82 ms,
+// now 1.05 ms (1.21 with two row blocks a wave and 32 columns a block); 128^3 480
+// -> 134 us; Hockney-Eastwood 64^3 float64 55 -> 29 us.  What bounds it: the
 // products (30 GFLOP, 0.68 ms alone) and on axis 0 the samples' float64
 // arithmetic run on the same units, so one does not hide the other; with the
 // library's sine and a division a sample cost 137 instructions, here about 35
-// (axis 0 972 -> 729 us).  Loops that fill LDS request eight (or compute four)
-// inputs at a time: one at a time axis 1 took 604 us.  16 instead of 32 columns
-// a block (four blocks a compute unit, twice the operand reads) changed nothing.
+// (axis 0 972 -> 729 us with the larger blocks).  Loops that fill LDS request
+// eight (or compute four) inputs at a time: one at a time axis 1 took 604 us.
 // Error against the transform in 80-bit arithmetic: below the six contractions'
 // for Vico-Greengard (16x24x32 1.4e-16 against 2.8e-16, 64^3 3.5e-16 against
 // 5.1e-16, 96x32x48 2.5e-16 against 4.5e-16), equal for Hockney-Eastwood.
@@ -187,8 +186,8 @@ __device__ __forceinline__ double column_tail(const AxisArgs& a, int J) {
 
 // VICO: the Vico-Greengard axis, else the DCT-I.  AXIS 0: inputs made here.
 // AXIS 2: results go to the octant.  NMAX bounds n (the LDS array); WAVES waves
-// share the rows, PBW 16-row blocks each; CG 16-column groups a block.
-template <bool VICO, int AXIS, int NMAX, int WAVES, int PBW, int CG>
+// take a 16-row block each; CG 16-column groups a block.
+template <bool VICO, int AXIS, int NMAX, int WAVES, int CG>
 __global__ __launch_bounds__(64 * WAVES) void k_green_axis(AxisArgs a) {
   constexpr int CT = 16 * CG, CP = CT + 1, NT = 64 * WAVES;
   __shared__ double lds[(NMAX + 1) * CP];
@@ -272,25 +271,21 @@ __global__ __launch_bounds__(64 * WAVES) void k_green_axis(AxisArgs a) {
     part[t] = s;
   }
   // ---- products
-  v4d acc[PBW][2][CG];
+  v4d acc[2][CG];
 #pragma unroll
-  for (int p = 0; p < PBW; ++p)
+  for (int o = 0; o < 2; ++o)
 #pragma unroll
-    for (int o = 0; o < 2; ++o)
-#pragma unroll
-      for (int g = 0; g < CG; ++g) acc[p][o][g] = v4d{0.0, 0.0, 0.0, 0.0};
-  const bool rows = wave < PB;  // a wave's blocks: wave, wave + WAVES (all there when PBW > 1)
+    for (int g = 0; g < CG; ++g) acc[o][g] = v4d{0.0, 0.0, 0.0, 0.0};
+  const bool rows = wave < PB;
   if (rows) {
     const double* im = a.image + wave * 128 + lane;
     const int sstep = PB * 128;
     // operands two steps ahead of their use
-    double nx[2][PBW][2];
+    double nx[2][2];
     auto load = [&](int s, int slot) {
       const int sc = s < KS ? s : KS - 1;
 #pragma unroll
-      for (int p = 0; p < PBW; ++p)
-#pragma unroll
-        for (int o = 0; o < 2; ++o) nx[slot][p][o] = im[(long long)sc * sstep + p * WAVES * 128 + o * 64];
+      for (int o = 0; o < 2; ++o) nx[slot][o] = im[(long long)sc * sstep + o * 64];
     };
     load(0, 0);
     load(1, 1);
@@ -305,20 +300,16 @@ __global__ __launch_bounds__(64 * WAVES) void k_green_axis(AxisArgs a) {
     };
     load_b(0, 0);
     auto step = [&](int s, int slot) {
-      double m[PBW][2];
+      double m[2];
 #pragma unroll
-      for (int p = 0; p < PBW; ++p)
-#pragma unroll
-        for (int o = 0; o < 2; ++o) m[p][o] = nx[slot][p][o];
+      for (int o = 0; o < 2; ++o) m[o] = nx[slot][o];
       load(s + 2, slot);
       load_b(s + 1, 1 - slot);
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
         for (int g = 0; g < CG; ++g)
-#pragma unroll
-          for (int p = 0; p < PBW; ++p)
-            acc[p][o][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[p][o], nb[slot][o][g], acc[p][o][g], 0, 0, 0);
+          acc[o][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[o], nb[slot][o][g], acc[o][g], 0, 0, 0);
     };
     int s = 0;
     for (; s + 1 < KS; s += 2) {
@@ -375,21 +366,19 @@ __global__ __launch_bounds__(64 * WAVES) void k_green_axis(AxisArgs a) {
   __syncthreads();
   if (rows) {
 #pragma unroll
-    for (int p = 0; p < PBW; ++p)
+    for (int r = 0; r < 4; ++r) {
+      const int k = wave * 16 + lane / 16 + 4 * r;
+      if (k < K) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int k = (wave + p * WAVES) * 16 + lane / 16 + 4 * r;
-        if (k < K) {
-#pragma unroll
-          for (int g = 0; g < CG; ++g) {
-            const int cc = 16 * g + lane % 16;
-            const double e = acc[p][0][g][r], o = acc[p][1][g][r];
-            const int m0 = VICO ? k : 2 * k, m1 = VICO ? n - k : 2 * k + 1;
-            lds[m0 * CP + cc] += VICO ? e + o : e;
-            lds[m1 * CP + cc] += VICO ? e - o : o;
-          }
+        for (int g = 0; g < CG; ++g) {
+          const int cc = 16 * g + lane % 16;
+          const double e = acc[0][g][r], o = acc[1][g][r];
+          const int m0 = VICO ? k : 2 * k, m1 = VICO ? n - k : 2 * k + 1;
+          lds[m0 * CP + cc] += VICO ? e + o : e;
+          lds[m1 * CP + cc] += VICO ? e - o : o;
         }
       }
+    }
   }
   if (t < CT) lds[(VICO ? K : n) * CP + t] += left[t];
   __syncthreads();
@@ -419,31 +408,35 @@ __global__ __launch_bounds__(64 * WAVES) void k_green_axis(AxisArgs a) {
   }
 }
 
-template <bool VICO, int AXIS, int NMAX, int WAVES, int PBW>
+// 32 columns a block reuse a matrix operand twice; 16 where 32 leave compute
+// units idle, and from n = 256 on, where the LDS of 32 leaves one or two blocks a
+// compute unit, whose fill and products then wait for each other (256^3
+// Hockney-Eastwood 455 -> 437 us, 384^3 Vico-Greengard 4590 -> 4380, 512^3 12440
+// -> 12140; 256^3 Vico-Greengard equal).
+template <bool VICO, int AXIS, int NMAX, int WAVES>
 hipError_t launch_size(const AxisArgs& a, hipStream_t s) {
-  // 32 columns a block reuse a matrix operand twice; 16 where 32 leave compute units idle
-  if (NMAX <= 128 && a.N < 32 * 512) {
-    if constexpr (NMAX <= 128)
-      hipLaunchKernelGGL((k_green_axis<VICO, AXIS, NMAX, WAVES, PBW, 1>), dim3((a.N + 15) / 16), dim3(64 * WAVES), 0, s,
-                         a);
+  static_assert(16 * WAVES >= NMAX / 2, "the waves cover the rows");
+  if (NMAX >= 256 || (NMAX <= 128 && a.N < 32 * 512)) {
+    if constexpr (NMAX != 192)
+      hipLaunchKernelGGL((k_green_axis<VICO, AXIS, NMAX, WAVES, 1>), dim3((a.N + 15) / 16), dim3(64 * WAVES), 0, s, a);
   } else {
-    hipLaunchKernelGGL((k_green_axis<VICO, AXIS, NMAX, WAVES, PBW, 2>), dim3((a.N + 31) / 32), dim3(64 * WAVES), 0, s,
-                       a);
+    if constexpr (NMAX < 256)
+      hipLaunchKernelGGL((k_green_axis<VICO, AXIS, NMAX, WAVES, 2>), dim3((a.N + 31) / 32), dim3(64 * WAVES), 0, s, a);
   }
   return hipGetLastError();
 }
 
-// The waves of a block take one 16-row block each, from n = 256 on two (so the
-// block's waves fill the compute unit's four SIMDs and a matrix operand serves
-// two column groups).
+// A wave takes one 16-row block: with two, as many waves again are missing to
+// hide the fill's and the samples' latency (two / one, Vico-Greengard: 256^3 1205
+// / 1055 us, 384^3 5720 / 4590, 512^3 12380 / 12400).
 template <bool VICO, int AXIS>
 hipError_t launch_axis(const AxisArgs& a, hipStream_t s) {
-  if (a.n <= 64) return launch_size<VICO, AXIS, 64, 4, 1>(a, s);
-  if (a.n <= 128) return launch_size<VICO, AXIS, 128, 4, 1>(a, s);
-  if (a.n <= 192) return launch_size<VICO, AXIS, 192, 6, 1>(a, s);
-  if (a.n <= 256) return launch_size<VICO, AXIS, 256, 4, 2>(a, s);
-  if (a.n <= 384) return launch_size<VICO, AXIS, 384, 6, 2>(a, s);
-  if (a.n <= 512) return launch_size<VICO, AXIS, 512, 8, 2>(a, s);
+  if (a.n <= 64) return launch_size<VICO, AXIS, 64, 4>(a, s);
+  if (a.n <= 128) return launch_size<VICO, AXIS, 128, 4>(a, s);
+  if (a.n <= 192) return launch_size<VICO, AXIS, 192, 6>(a, s);
+  if (a.n <= 256) return launch_size<VICO, AXIS, 256, 8>(a, s);
+  if (a.n <= 384) return launch_size<VICO, AXIS, 384, 12>(a, s);
+  if (a.n <= 512) return launch_size<VICO, AXIS, 512, 16>(a, s);
   return hipErrorInvalidValue;
 }
 

@@ -257,10 +257,11 @@ inline ColArgs conv_gather(const ColArgs& a, int tc) {
 // halves the reads of the octant; on a grid of fewer than CONV_SINGLE_BLOCKS
 // blocks (four a CU) that chain is what the pass waits for, and each set gets
 // a block of its own.  Whole solves, paired / single: 48^3 f64 28.8 / 27.3 us,
-// 64^3 f64 36.9 / 34.0, 64^3 f32 27.6 / 25.1, 96^3 f64 61.2 / 59.6, 96^3 f32 40.4 / 39.3, 256x64x64
-// f32 48.2 / 45.5; on larger launches it loses: 48x192x96 f64 (1261 blocks)
-// 56.3 / 57.1, nineteen 32^3 f32 in a batch (1254) 39.9 / 41.5, six 96^3 f32
-// (2328) 133.8 / 138.3.  Grids whose lone column is gathered are larger still.
+// 64^3 f64 36.9 / 34.0, 64^3 f32 27.6 / 25.1, 96^3 f64 61.2 / 59.6, 96^3 f32
+// 40.4 / 39.3, 256x64x64 f32 48.2 / 45.5; on larger launches it loses: 48x192x96
+// f64 (1261 blocks) 56.3 / 57.1, nineteen 32^3 f32 in a batch (1254) 39.9 / 41.5,
+// six 96^3 f32 (2328) 133.8 / 138.3.  Grids whose lone column is gathered are
+// larger still.
 constexpr long long CONV_SINGLE_BLOCKS = 1024;
 inline ColArgs conv_single(const ColArgs& a, int items) {
   ColArgs b = a;
