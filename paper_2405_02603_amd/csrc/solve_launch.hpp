@@ -213,11 +213,17 @@ hipError_t launch_p5(int LC, int v, const RowArgs& a, int items, hipStream_t s) 
 
 // Axis-0 pass of the gradient solve.  Variants 0 and 1: one launch writes
 // every output from one forward transform, the spectrum held in registers
-// through the outputs; for pencils of 256 and more variant 0 spreads a pencil
-// over more threads, with plan 1: up to 1024 threads a block through 512
-// (radix-8 stages), 512 threads beyond (a 1024-thread block is held to 128
-// registers a thread); variant 1 is the column pass's variant 1.  Variant 2:
-// one launch per output in the column pass's variant-0 shape (each reads the
+// through the outputs.  Variant 0, pencils of 256 to 512: plan 1 over up to
+// 1024 threads a block (radix-8 stages).  Beyond, float32: plan 1 over 512
+// threads; float64: the two-stage plan, 32 threads a pencil.  64 threads are
+// held to 256 registers of which the spectrum and an output take most, and at
+// 768 points half of them have no butterfly: (64 / 32 threads) 384^3 25.0 ms
+// with 1,044 bytes a lane of scratch / 8.6 without, 512^3 27.9 / 21.0, 384 x 32
+// x 32 275 / 80 us, 512 x 32 x 32 140 / 121.
+// Variant 1 is the column pass's variant 0 where that is the two-stage plan
+// that variant 1 was before (float64 192^3 925 us; 2,248 with the three-stage
+// plan, which spills with four outputs), else its variant 1.  Variant 2: one
+// launch per output in the column pass's variant-0 shape (each reads the
 // spectrum again, with fewer registers).  The tile stays col_tc (the layout
 // of the tables).
 template <typename T>
@@ -226,8 +232,9 @@ __host__ __device__ constexpr TileCfg grad_cfg(int L, int v) {
   // (384: plan 0, whose first stages have 24 and 48 butterflies; plan 1's
   // radix-24 stage has only 16)
   if (v == 0 && L >= 256 && L <= 512) return {L == 384 ? 0 : 1, tc, 1024 / tc < L / 8 ? 1024 / tc : L / 8};
-  if (v == 0 && L > 512) return {1, tc, 512 / tc};
-  return conv_shape<T>(L, v == 2 ? 0 : v);
+  if (v == 0 && L > 512) return sizeof(T) == 8 ? TileCfg{L == 768 ? 1 : 0, tc, 32} : TileCfg{1, tc, 512 / tc};
+  const bool swapped = L == 24 || L == 48 || L == 96 || L == 192 || L == 384;
+  return conv_shape<T>(L, v == 2 || swapped ? 0 : v);
 }
 
 template <typename T>
