@@ -150,19 +150,24 @@ __device__ __forceinline__ cx<T> ld_once(const cx<T>* p) {
 //       192^3 float32 (123 MB) 172.8 -> 176.0.
 //     the inverse row loads, from 100 MB: 256^3 float64 P5 93 -> 75; below,
 //       128^3 62.4 -> 64.1, two 128^3 102.8 -> 106.5.
+//     the float64 forward row stores, from 600 MB (the half of S they write is
+//       then beyond the cache): float64 sixteen 128^3 1498 -> 1445, three
+//       192^3 976 -> 960; equal at 540 MB (eight 128^3, one 256^3), below, four
+//       128^3 333 -> 338, 192^3 323 -> 330.
 //   By type and length:
-//     the forward row stores, rows of 384 and more (half of S is then beyond
-//       the cache at once): 512^3 float32 P1 + P2 1035 -> 986; 256^3 float32
-//       122 -> 135.
+//     the forward row stores, rows of 384 and more: 512^3 float32 P1 + P2
+//       1035 -> 986; 256^3 float32 122 -> 135.
 //     the axis-0 loads, except float32 pencils of 512 and more: float64 256^3
 //       738 -> 717, 384^3 4710 -> 4470, sixteen float32 128^3 756 -> 737; but
 //       float32 512^3 3442 -> 3581.
 enum StreamBits {
   STREAM_COL_STORE = 1,
-  STREAM_ROW_LOAD = 2
+  STREAM_ROW_LOAD = 2,
+  STREAM_ROW_STORE = 4
 };
 constexpr long long STREAM_COL_STORE_MIN = 200000000;  // bytes of S in the launch group
 constexpr long long STREAM_ROW_LOAD_MIN = 100000000;
+constexpr long long STREAM_ROW_STORE_MIN = 600000000;
 
 __host__ __device__ constexpr bool stream_row_store(int n2) { return n2 >= 384; }
 template <typename T>
@@ -909,7 +914,9 @@ __global__ __launch_bounds__(NT) void k_slab_conv(SlabArgs a) {
 //   X[k] = (Z[k] + conj Z[LC-k]) / 2 - i e^{-i pi k / LC} (Z[k] - conj Z[LC-k]) / 2.
 // A block transforms G groups of TR rows, one after the other, and requests
 // every group's input first: a thread keeps G times the bytes in flight.
-template <typename T, int LC, int PID, int TR, int NQ, int G = 1>
+// STREAM: the results are streamed past the caches (a kernel of its own: with a
+// branch on a flag the float32 256-point rows took 10 us longer).
+template <typename T, int LC, int PID, int TR, int NQ, int G, bool STREAM>
 __global__ __launch_bounds__(TR* NQ) void k_row_r2c(RowArgs a) {
   constexpr int K = plan_len(LC, PID);
   constexpr int LP = row_pitch(LC);
@@ -985,7 +992,7 @@ __global__ __launch_bounds__(TR* NQ) void k_row_r2c(RowArgs a) {
           const cx<T> E = {T(0.5) * (A.x + B.x), T(0.5) * (A.y + B.y)};
           const cx<T> D = {T(0.5) * (A.x - B.x), T(0.5) * (A.y - B.y)};
           const cx<T> U = cmul(pp[k], D);
-          put<stream_row_store(LC)>(&out[k], cx<T>{E.x + U.y, E.y - U.x});
+          put<STREAM>(&out[k], cx<T>{E.x + U.y, E.y - U.x});
         }
       }
     }

@@ -180,8 +180,13 @@ hipError_t launch_p1(int LC, int v, const RowArgs& a, int items, hipStream_t s) 
   if (LC == LV && v == VV) {                                                                        \
     constexpr TileCfg c = row_cfg<T>(LV, VV);                                                       \
     const int blocks = (a.nrows + c.tiles * c.groups - 1) / (c.tiles * c.groups);                   \
-    hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups>), dim3(blocks, items),      \
-                       dim3(c.tiles * c.nq), 0, s, a);                                              \
+    constexpr bool always = stream_row_store(LV), by_size = sizeof(T) == 8 && !always;              \
+    if (by_size && (a.stream & STREAM_ROW_STORE))                                                   \
+      hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups, always || by_size>),     \
+                         dim3(blocks, items), dim3(c.tiles * c.nq), 0, s, a);                       \
+    else                                                                                            \
+      hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups, always>),                \
+                         dim3(blocks, items), dim3(c.tiles * c.nq), 0, s, a);                       \
     found = true;                                                                                   \
   }
 #define FSP_CASE(LV) FSP_VARIANTS(FSP_CASE_V, LV)
@@ -466,10 +471,13 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
     t.g_k1_stride = (long long)((g.n2 + t.gt) / t.gt) * (g.n0 + 1) * t.gt;
     return launch_tiny<T>(t, g.items, s);
   }
-  // spectra of this group together: what the caches would have to hold
-  const long long s_bytes = (long long)(g.nout ? g.nout : g.items) * g.n0 * plane * (long long)sizeof(cx<T>);
+  // spectra of this group together: what the caches would have to hold (the
+  // gradient's forward passes write one)
+  const long long s_one = (long long)g.n0 * plane * (long long)sizeof(cx<T>);
+  const long long s_bytes = (g.nout ? g.nout : g.items) * s_one;
   const int stream = (s_bytes >= STREAM_COL_STORE_MIN ? STREAM_COL_STORE : 0) |
-                     (s_bytes >= STREAM_ROW_LOAD_MIN ? STREAM_ROW_LOAD : 0);
+                     (s_bytes >= STREAM_ROW_LOAD_MIN ? STREAM_ROW_LOAD : 0) |
+                     (g.items * s_one >= STREAM_ROW_STORE_MIN ? STREAM_ROW_STORE : 0);
   RowArgs ra{};
   ra.items = g.items_dev;
   ra.stream = stream;
