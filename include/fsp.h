@@ -221,13 +221,16 @@ fsp_status fsp_solve_grad(fsp_plan p, const void* rho, void* phi, void* grad, vo
  * fsp_solve_passes then accepts only ranges that contain both passes of such
  * a pair or neither (FSP_ERR_INVALID_ARG otherwise).  The plane pairs and the
  * fused schedule exclude each other.
- * All zeros let the library pick: whole solves and gradients on grids with
- * n1 == n2 in {32, 48, 64} then run both plane pairs, which are the faster
- * there for any number of solves, and whole solves whose spectrum fits in LDS
- * (n0, n1 <= 16, n2 <= 32) one kernel; passes asked for one by one stay separate.
- * Results are identical up to rounding order across schedules.  A new plan starts
- * with the schedule last tuned for its grid and precision in this process (else
- * all zeros). */
+ * Results are identical up to rounding order across schedules.  Which kernel a
+ * variant's number names may change between versions of this library.
+ * A new plan starts with the schedule last tuned for its grid and precision in
+ * this process.  Else it has none: get returns all zeros, and until one is set or
+ * tuned the library picks the kernels.  Each pass then runs its variant 0, but
+ * whole solves and gradients on grids with n1 == n2 in {32, 48, 64} run both
+ * plane pairs, which are the faster there for any number of solves, and whole
+ * solves whose spectrum fits in LDS (n0, n1 <= 16, n2 <= 32) one kernel; passes
+ * asked for one by one stay separate.  All zeros that are set are a schedule
+ * like any other: variant 0 of each pass, five kernels. */
 fsp_status fsp_plan_get_schedule(fsp_plan p, int* variants /* [5] */);
 fsp_status fsp_plan_set_schedule(fsp_plan p, const int* variants /* [5] */);
 
@@ -243,10 +246,11 @@ fsp_status fsp_plan_set_schedule(fsp_plan p, const int* variants /* [5] */);
  * `stream`.  times_ms (NULL or [5 * 3 + 5]) receives the median time of each
  * variant, times_ms[pass * 3 + variant], then the median time of whole solves
  * with schedules built from the best variants: times_ms[15] passes 1-3 fused,
- * [16] the fastest variant of each pass (separate passes, unless all are 0 and
- * that schedule picks other kernels), [17] both plane pairs (0-1 and 3-4), [18] the
+ * [16] all passes separate, [17] both plane pairs (0-1 and 3-4), [18] the
  * plane pair 0-1 alone, [19] the pair 3-4 alone (0 where the schedule is not
- * supported); the fastest of these schedules is kept.  On a plan with
+ * supported); the fastest of these schedules is kept, or, where whole solves fit
+ * in LDS, no schedule if the one kernel picked there is faster still (get then
+ * returns all zeros).  On a plan with
  * FSP_WANT_GRAD it also times the gradient solve's axis-0 pass (four outputs)
  * in each of its variants and keeps the fastest for fsp_solve_grad
  * (fsp_plan_set_schedule drops that choice: the gradient then follows the
@@ -270,7 +274,8 @@ fsp_status fsp_solve_batched(int count, const fsp_plan* plans, const void* const
  * 1 <= reps <= 8, median) with the separate passes fsp_autotune last found
  * fastest for that grid (else the first plan's) and, on a grid that supports
  * the plane kernels, with the plane kernel for passes 0-1, for passes 3-4,
- * and for both, the axis-0 variant as last tuned.  From the fastest, each pass
+ * and for both, the axis-0 variant as last tuned; where whole solves fit in LDS
+ * also with the one kernel that is picked there.  From the fastest, each pass
  * that is not a plane kernel then tries its other variants in turn, each
  * timed the same way, and keeps one only if the group runs faster.  The
  * result is set on every plan of the group.  Groups whose tuned schedule is
@@ -356,7 +361,7 @@ fsp_status fsp_plan_octant_offset(fsp_plan p, int component, size_t* offset);
 /* Model bytes that one solve moves through HBM with this plan's schedule
  * (reads + writes of its kernels, the Green's octant included: five passes,
  * fewer where the fused slab or a plane pair of the schedule keeps intermediates
- * in LDS; all zeros count as five passes): the
+ * in LDS; five passes while the plan has none and the library picks): the
  * memory traffic against which Section 3.4 finds the solve memory-bound. */
 fsp_status fsp_plan_model_bytes(fsp_plan p, double* bytes);
 

@@ -242,7 +242,8 @@ class Plan:
 
     @property
     def schedule(self):
-        """Variant of each of the five passes."""
+        """Variant of each of the five passes (all 0 too while none is set or tuned and the library
+        picks the kernels; setting [0] * 5 chooses variant 0 of each pass)."""
         arr = (ctypes.c_int * 5)()
         check(self._lib.fsp_plan_get_schedule(self._h, arr), "fsp_plan_get_schedule")
         return list(arr)

@@ -274,6 +274,7 @@ struct fsp_plan_s {
   int grad_p3 = -1;         // axis-0 variant of the gradient solve (-1: from the schedule)
   size_t work1_bytes = 0;   // one workspace S (the gradient's other spectra follow it)
   int var[5]{};  // schedule variant of each pass
+  bool picked = true;  // no schedule set or tuned: all zeros, and whole solves take the kernels picked for their grid
   int sep[5]{};  // the fastest separate-pass variants found by fsp_autotune (whatever schedule it kept)
   size_t ghat_bytes = 0, work_bytes = 0, pre_bytes = 0;
   std::vector<char> tw_host;      // image of [0, oct_off) of the Green's buffer
@@ -362,15 +363,22 @@ struct TuneKey {
   }
 };
 std::mutex g_tune_mu;
-std::map<TuneKey, std::array<int, 11>> g_tuned;  // schedule, the gradient's axis-0 variant, separate variants
+struct Tuned {
+  int var[5];
+  bool picked;
+  int grad_p3;
+  int sep[5];
+};
+std::map<TuneKey, Tuned> g_tuned;
 
+// Whether whole solves can run as one kernel.
 bool tiny_supported(const fsp_plan_s* p) {
   if (p->chunks != 1) return false;
   return p->d.prec == FSP_F64 ? fsp::tiny_supported<double>(p->n[0], p->n[1], p->n[2])
                               : fsp::tiny_supported<float>(p->n[0], p->n[1], p->n[2]);
 }
 
-// Whole solves, and gradients, on the default variants (all 0) run passes 0-1
+// Whole solves, and gradients, of plans whose kernels are picked run passes 0-1
 // and 3-4 as plane kernels at 32, 48 and 64 points, whose planes are one column
 // tile.  There the pairs were the faster, or equal, at every count measured
 // (separate / planes): one solve of 32^3 f32 23.5 / 15.7 us, 48^3 23.6 / 20.4,
@@ -378,8 +386,7 @@ bool tiny_supported(const fsp_plan_s* p) {
 // 143 / 94, 385 / 324, 865 / 702, f64 195 / 151, 670 / 565, 732 (64 solves) / 609;
 // gradients 28.5 / 24.0, 43.2 / 38.5, 44.3 / 38.1.  At 96 they are not (41.8 / 54).
 bool default_planes(const fsp_plan_s* p) {
-  if (p->n[1] != p->n[2] || p->chunks != 1) return false;
-  if (std::any_of(p->var, p->var + 5, [](int v) { return v != 0; })) return false;
+  if (!p->picked || p->n[1] != p->n[2] || p->chunks != 1) return false;
   return p->d.prec == FSP_F64 ? fsp::plane_default<double>(p->n[2]) : fsp::plane_default<float>(p->n[2]);
 }
 
@@ -388,7 +395,7 @@ double model_bytes(const fsp_plan_s* p) {
   // P3 reads/writes 2 n1 (n2+1) n0 and reads the octant; P4 mirrors P2, P5 mirrors P1.
   // The fused slab (passes 1-3) reads and writes the (n2+1) n1 n0 rows once; a
   // plane pair reads rho and writes S (0-1), or reads S and writes phi (3-4).
-  // All zeros count as the five passes, whichever kernels they run as.
+  // A plan whose kernels are picked counts as the five passes.
   const double n0 = p->n[0], n1 = p->n[1], n2 = p->n[2], s = p->rb;
   const double real_grid = n0 * n1 * n2;
   const double half1 = n0 * n1 * (n2 + 1) * 2;      // reals in (n2+1) n1 n0 complex
@@ -507,9 +514,10 @@ fsp_status fsp_plan_create(const fsp_plan_desc* desc, fsp_plan* out) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(TuneKey{p->n[0], p->n[1], p->n[2], d.prec});
     if (it != g_tuned.end()) {
-      for (int i = 0; i < 5; ++i) p->var[i] = it->second[i];
-      p->grad_p3 = it->second[5];
-      for (int i = 0; i < 5; ++i) p->sep[i] = it->second[6 + i];
+      std::copy_n(it->second.var, 5, p->var);
+      std::copy_n(it->second.sep, 5, p->sep);
+      p->picked = it->second.picked;
+      p->grad_p3 = it->second.grad_p3;
     }
   }
   // the column kernels address a pencil's rows with 32-bit element offsets
@@ -905,13 +913,16 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
 // Shape fields shared by every item of a launch group (items filled by the caller).
 static fsp::SolveGeom group_geom(const fsp_plan_s* p, const int* var);
 
-// Shape fields for passes first..last of the plan's schedule: whole solves on
-// the default variants take the plane kernels where those are the faster for
-// every number of items (default_planes).
+// Shape fields for passes first..last of the plan's schedule.  Whole solves of a
+// plan whose kernels are picked take the plane kernels where those are the faster
+// for every number of items (default_planes), and one kernel on tiny grids.
 static fsp::SolveGeom group_geom(const fsp_plan_s* p, int first = 0, int last = 4) {
   constexpr int P = fsp::PLANE;
   constexpr int planes[5] = {P, P, 0, P, P};
-  return group_geom(p, first == 0 && last == 4 && default_planes(p) ? planes : p->var);
+  const bool whole = first == 0 && last == 4;
+  fsp::SolveGeom g = group_geom(p, whole && default_planes(p) ? planes : p->var);
+  g.tiny = whole && p->picked && tiny_supported(p);
+  return g;
 }
 
 // Shape fields with an explicit schedule.
@@ -970,7 +981,7 @@ static bool same_shape(const fsp_plan_s* a, const fsp_plan_s* b) {
               a->pitch == b->pitch && a->plane == b->plane && a->chunks == b->chunks &&
               a->gather_min == b->gather_min;
   for (int i = 0; i < 5; ++i) same = same && a->var[i] == b->var[i];
-  return same;
+  return same && a->picked == b->picked;
 }
 
 static hipError_t run_group(const fsp::SolveGeom& g, bool f64, int first, int last, hipStream_t s) {
@@ -1219,6 +1230,7 @@ fsp_status fsp_plan_set_schedule(fsp_plan p, const int* variants) {
       return fail(FSP_ERR_INVALID_ARG, "fsp_plan_set_schedule: variant out of range");
   }
   for (int i = 0; i < 5; ++i) p->var[i] = variants[i];
+  p->picked = false;
   p->grad_p3 = -1;  // the gradient solve follows this schedule
   return FSP_OK;
 }
@@ -1246,8 +1258,18 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
   hipEvent_t e0 = nullptr, e1 = nullptr;
   e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
-  int best[5];
-  for (int i = 0; i < 5; ++i) best[i] = p->var[i];
+  int best[5], orig[5];
+  std::copy_n(p->var, 5, best);
+  std::copy_n(p->var, 5, orig);
+  const bool orig_picked = p->picked;
+  p->picked = false;  // the schedules below are timed as they stand
+  auto fail_tuning = [&](fsp_status st) {
+    std::copy_n(orig, 5, p->var);
+    p->picked = orig_picked;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    return st;
+  };
   if (best[1] == fsp::FUSED) best[1] = best[2] = best[3] = 0;  // tune the separate passes first
   if (best[0] == fsp::PLANE) best[0] = best[1] = 0;
   if (best[3] == fsp::PLANE) best[3] = best[4] = 0;
@@ -1265,12 +1287,7 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
         if (st == FSP_OK && e == hipSuccess) st = solve_one(p, rho, phi, s, pass, pass);
         if (st == FSP_OK && e == hipSuccess) e = hipEventRecord(e1, s);
         if (st == FSP_OK && e == hipSuccess && pass < 4) st = solve_one(p, rho, phi, s, pass + 1, 4);
-        if (st != FSP_OK) {  // the solve's own error is the one reported
-          for (int i = 0; i < 5; ++i) p->var[i] = best[i];
-          if (e0) (void)hipEventDestroy(e0);
-          if (e1) (void)hipEventDestroy(e1);
-          return st;
-        }
+        if (st != FSP_OK) return fail_tuning(st);  // the solve's own error is the one reported
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
@@ -1285,13 +1302,16 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
     }
   }
   for (int i = 0; i < 5; ++i) p->sep[i] = best[i];
+  bool best_picked = false;
   // whole-solve schedules built from the best separate variants: the separate
   // passes, the fused slab (passes 1-3), the plane kernels for passes 0-1 and
-  // 3-4 (both pairs, or either alone); each timed as a full solve, the fastest kept
+  // 3-4 (both pairs, or either alone), and on tiny grids the one kernel that is
+  // picked there; each timed as a full solve, the fastest kept
   if (e == hipSuccess) {
     fsp_status st_sched = FSP_OK;
-    auto time_solve = [&](const int* sched, float* out) -> hipError_t {
-      for (int i = 0; i < 5; ++i) p->var[i] = sched[i];
+    auto time_solve = [&](const int* sched, bool picked, float* out) -> hipError_t {
+      std::copy_n(sched, 5, p->var);
+      p->picked = picked;
       hipError_t r = hipSuccess;
       float rep_ms[8] = {};
       for (int k = 0; k <= reps && r == hipSuccess; ++k) {
@@ -1312,24 +1332,20 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
                             {P, P, best[2], P, P},
                             {P, P, best[2], best[3], best[4]},
                             {best[0], best[1], best[2], P, P},
-                            {0, 0, 0, 0, 0}};  // tiny grids: the whole solve in one launch
+                            {0, 0, 0, 0, 0}};  // as picked: the whole solve in one launch
+    constexpr int PICKED = 5;
     const bool ok[6] = {true,
                         fused_supported(p),
                         plane_supported(p),
                         plane_supported(p),
                         plane_supported(p),
-                        tiny_supported(p) && std::any_of(best, best + 5, [](int v) { return v != 0; })};
+                        tiny_supported(p)};
     float t[6] = {0, 0, 0, 0, 0, 0};
     int pick = 0;
     for (int c = 0; c < 6 && e == hipSuccess; ++c) {
       if (!ok[c]) continue;
-      e = time_solve(cand[c], &t[c]);
-      if (st_sched != FSP_OK) {
-        for (int i = 0; i < 5; ++i) p->var[i] = best[i];
-        if (e0) (void)hipEventDestroy(e0);
-        if (e1) (void)hipEventDestroy(e1);
-        return st_sched;
-      }
+      e = time_solve(cand[c], c == PICKED, &t[c]);
+      if (st_sched != FSP_OK) return fail_tuning(st_sched);
       if (e == hipSuccess && t[c] < t[pick]) pick = c;
     }
     if (times_ms) {
@@ -1337,10 +1353,13 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
       times_ms[5 * fsp::NUM_VARIANTS + 1] = t[0];
       for (int c = 2; c < 5; ++c) times_ms[5 * fsp::NUM_VARIANTS + c] = t[c];
     }
-    if (e == hipSuccess)
-      for (int i = 0; i < 5; ++i) best[i] = cand[pick][i];
+    if (e == hipSuccess) {
+      std::copy_n(cand[pick], 5, best);
+      best_picked = pick == PICKED;
+    }
   }
-  for (int i = 0; i < 5; ++i) p->var[i] = best[i];
+  std::copy_n(best, 5, p->var);
+  p->picked = best_picked;
   // the gradient solve's axis-0 pass (four outputs), each of its variants
   if (e == hipSuccess && p->grad) {
     const bool f64 = p->d.prec == FSP_F64;
@@ -1364,20 +1383,22 @@ fsp_status fsp_autotune(fsp_plan p, const void* rho, void* phi, int reps, void* 
     }
     if (e == hipSuccess) p->grad_p3 = best_v;
   }
-  if (e0) (void)hipEventDestroy(e0);
-  if (e1) (void)hipEventDestroy(e1);
-  if (e != hipSuccess) return fail_hip(e, "fsp_autotune");
+  if (e != hipSuccess) return fail_tuning(fail_hip(e, "fsp_autotune"));
+  (void)hipEventDestroy(e0);
+  (void)hipEventDestroy(e1);
   // leave a correct result in phi with the tuned schedule
   fsp_status st = solve_one(p, rho, phi, s);
   if (st != FSP_OK) return st;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    std::array<int, 11> a;
-    for (int i = 0; i < 5; ++i) a[i] = best[i];
-    auto it = g_tuned.find(TuneKey{p->n[0], p->n[1], p->n[2], p->d.prec});
-    a[5] = p->grad ? p->grad_p3 : it != g_tuned.end() ? it->second[5] : -1;
-    for (int i = 0; i < 5; ++i) a[6 + i] = p->sep[i];
-    g_tuned[TuneKey{p->n[0], p->n[1], p->n[2], p->d.prec}] = a;
+    const TuneKey key{p->n[0], p->n[1], p->n[2], p->d.prec};
+    Tuned a{};
+    std::copy_n(best, 5, a.var);
+    std::copy_n(p->sep, 5, a.sep);
+    a.picked = best_picked;
+    auto it = g_tuned.find(key);
+    a.grad_p3 = p->grad ? p->grad_p3 : it != g_tuned.end() ? it->second.grad_p3 : -1;
+    g_tuned[key] = a;
   }
   return FSP_OK;
 }
@@ -1431,15 +1452,22 @@ fsp_status fsp_autotune_batch(int count, const fsp_plan* plans, const void* cons
       std::lock_guard<std::mutex> lk(g_tune_mu);
       auto it = g_tuned.find(TuneKey{p0->n[0], p0->n[1], p0->n[2], p0->d.prec});
       if (it != g_tuned.end())
-        for (int k = 0; k < 5; ++k) base[k] = it->second[k], sp[k] = it->second[6 + k];
+        for (int k = 0; k < 5; ++k) base[k] = it->second.var[k], sp[k] = it->second.sep[k];
     }
     if (base[1] == fsp::FUSED) continue;  // the fused slab: nothing to choose between
-    std::vector<std::array<int, 5>> orig;
-    for (fsp_plan q : gp) orig.push_back({q->var[0], q->var[1], q->var[2], q->var[3], q->var[4]});
+    struct Schedule {
+      int var[5];
+      bool picked;
+    };
+    auto set = [](fsp_plan q, const Schedule& c) {
+      std::copy_n(c.var, 5, q->var);
+      q->picked = c.picked;
+    };
+    std::vector<Schedule> orig;
+    for (fsp_plan q : gp) orig.push_back({{q->var[0], q->var[1], q->var[2], q->var[3], q->var[4]}, q->picked});
     // median time of the group's solves enqueued together with schedule c
-    auto time_group = [&](const int* c, float* out) {
-      for (fsp_plan q : gp)
-        for (int k = 0; k < 5; ++k) q->var[k] = c[k];
+    auto time_group = [&](const Schedule& c, float* out) {
+      for (fsp_plan q : gp) set(q, c);
       float rep_ms[8] = {};
       for (int r = 0; r <= reps && e == hipSuccess; ++r) {  // r == 0 warms up
         e = hipEventRecord(e0, s);
@@ -1456,42 +1484,43 @@ fsp_status fsp_autotune_batch(int count, const fsp_plan* plans, const void* cons
       *out = median_ms(rep_ms, reps);
     };
     const int P = fsp::PLANE;
-    const bool tiny = tiny_supported(p0);  // whole solves in one launch; such grids have no plane kernels
-    const int cand[4][5] = {{sp[0], sp[1], base[2], sp[3], sp[4]},
-                            {tiny ? 0 : P, tiny ? 0 : P, tiny ? 0 : base[2], tiny ? 0 : sp[3], tiny ? 0 : sp[4]},
-                            {sp[0], sp[1], base[2], P, P},
-                            {P, P, base[2], P, P}};
-    const int ncand = plane_supported(p0) ? 4 : tiny ? 2 : 1;
+    const bool tiny = tiny_supported(p0);  // whole solves in one launch, as picked; such grids have no plane kernels
+    std::vector<Schedule> cand{{{sp[0], sp[1], base[2], sp[3], sp[4]}, false}};
+    if (plane_supported(p0)) {
+      cand.push_back({{P, P, base[2], sp[3], sp[4]}, false});
+      cand.push_back({{sp[0], sp[1], base[2], P, P}, false});
+      cand.push_back({{P, P, base[2], P, P}, false});
+    }
+    if (tiny) cand.push_back({{0, 0, 0, 0, 0}, true});
     float best_ms = 1e30f;
-    int cur[5] = {cand[0][0], cand[0][1], cand[0][2], cand[0][3], cand[0][4]};
+    Schedule cur = cand[0];
     bool timed = false;
-    for (int c = 0; c < ncand && e == hipSuccess && st == FSP_OK; ++c) {
+    for (size_t c = 0; c < cand.size() && e == hipSuccess && st == FSP_OK; ++c) {
       float ms = 0;
       time_group(cand[c], &ms);
       if (e == hipSuccess && st == FSP_OK && ms < best_ms) {
         best_ms = ms, timed = true;
-        for (int k = 0; k < 5; ++k) cur[k] = cand[c][k];
+        cur = cand[c];
       }
     }
     // then each separate pass in turn: its other variants, timed with the group
     // (a variant that wins alone need not win when the group's launches are
     // wider, e.g. where occupancy decides)
-    for (int q = 0; q < 5 && timed && e == hipSuccess && st == FSP_OK; ++q) {
-      if (cur[q] == P) continue;
+    for (int q = 0; q < 5 && timed && !cur.picked && e == hipSuccess && st == FSP_OK; ++q) {
+      if (cur.var[q] == P) continue;
       for (int v = 0; v < fsp::NUM_VARIANTS && e == hipSuccess && st == FSP_OK; ++v) {
-        if (v == cur[q]) continue;
-        int trial[5] = {cur[0], cur[1], cur[2], cur[3], cur[4]};
-        trial[q] = v;
+        if (v == cur.var[q]) continue;
+        Schedule trial = cur;
+        trial.var[q] = v;
         float ms = 0;
         time_group(trial, &ms);
         if (e == hipSuccess && st == FSP_OK && ms < best_ms) {
           best_ms = ms;
-          cur[q] = v;
+          cur = trial;
         }
       }
     }
-    for (size_t m = 0; m < gp.size(); ++m)
-      for (int k = 0; k < 5; ++k) gp[m]->var[k] = timed ? cur[k] : orig[m][k];
+    for (size_t m = 0; m < gp.size(); ++m) set(gp[m], timed ? cur : orig[m]);
     if (st != FSP_OK) break;
   }
   if (e0) (void)hipEventDestroy(e0);

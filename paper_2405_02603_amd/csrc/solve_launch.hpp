@@ -420,6 +420,7 @@ struct SolveGeom {
   const void* tw_c1[5];      // twiddles of length 2 n1 for the plan of P2 / P4
   const void* tw_c0;         // twiddles of length 2 n0 for the plan of P3
   const void* split;         // exp(-i pi k / n2), k in [0, n2]
+  bool tiny;                 // whole solves as one kernel (var: the separate passes)
   const void* ghat[MAX_ITEMS];  // octant of each item, blocked [n1+1][tiles][n0+1][TC of P3]
   void* work[MAX_ITEMS];        // S of each item
   const void* rho[MAX_ITEMS];
@@ -434,13 +435,6 @@ struct SolveGeom {
   void* ophi[MAX_OUT];          // result of each output
 };
 
-template <typename T>
-bool tiny_whole(const SolveGeom& g) {
-  bool plain = g.nout == 0 && g.chunks == 1;
-  for (int v : g.var) plain = plain && v == 0;
-  return plain && tiny_supported<T>(g.n0, g.n1, g.n2);
-}
-
 // Passes first..last of one solve (0 = P1 ... 4 = P5).
 template <typename T>
 hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) {
@@ -451,11 +445,11 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   if (!tab && (g.items < 1 || g.items > MAX_ITEMS)) return hipErrorInvalidValue;
   if (tab && (g.items < 1 || g.items > 65535 || g.nout)) return hipErrorInvalidValue;
   const int nfill = tab ? 0 : g.items;
-  // Whole solves of a plan on its default variants whose spectrum fits in LDS:
+  // Whole solves whose spectrum fits in LDS, of a plan whose kernels are picked:
   // one launch.  The line lies where LDS ends; below it one launch is the faster
   // everywhere (pipelined solves of 8^3 23.1 -> 10.1 us, of 16^3 float64 23.8 ->
   // 16.1, of 16x16x32 float32, the largest, 23.8 -> 18.2).
-  if (first == 0 && last == 4 && tiny_whole<T>(g)) {
+  if (first == 0 && last == 4 && g.tiny) {
     TinyArgs t{};
     t.items = g.items_dev;
     for (int i = 0; i < nfill; ++i) {
