@@ -390,21 +390,33 @@ bool default_planes(const fsp_plan_s* p) {
   return p->d.prec == FSP_F64 ? fsp::plane_default<double>(p->n[2]) : fsp::plane_default<float>(p->n[2]);
 }
 
-double model_bytes(const fsp_plan_s* p) {
+// Bytes that a whole solve with schedule `var` moves.
+double schedule_bytes(const fsp_plan_s* p, const int* var) {
   // P1 reads rho, writes (n2+1) n1 n0 complex; P2 reads that, writes 2 n1 (n2+1) n0;
   // P3 reads/writes 2 n1 (n2+1) n0 and reads the octant; P4 mirrors P2, P5 mirrors P1.
   // The fused slab (passes 1-3) reads and writes the (n2+1) n1 n0 rows once; a
   // plane pair reads rho and writes S (0-1), or reads S and writes phi (3-4).
-  // A plan whose kernels are picked counts as the five passes.
   const double n0 = p->n[0], n1 = p->n[1], n2 = p->n[2], s = p->rb;
   const double real_grid = n0 * n1 * n2;
   const double half1 = n0 * n1 * (n2 + 1) * 2;      // reals in (n2+1) n1 n0 complex
   const double half2 = n0 * 2 * n1 * (n2 + 1) * 2;  // reals in 2 n1 (n2+1) n0 complex
   const double octant = (n0 + 1) * (n1 + 1) * (n2 + 1);
-  if (p->var[1] == fsp::FUSED) return (2 * real_grid + 4 * half1 + octant) * s;
-  const double fwd = p->var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
-  const double inv = p->var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  if (var[1] == fsp::FUSED) return (2 * real_grid + 4 * half1 + octant) * s;
+  const double fwd = var[0] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
+  const double inv = var[3] == fsp::PLANE ? real_grid + half2 : real_grid + 2 * half1 + half2;
   return (fwd + 2 * half2 + octant + inv) * s;
+}
+
+constexpr int PLANE_PAIRS[5] = {fsp::PLANE, fsp::PLANE, 0, fsp::PLANE, fsp::PLANE};
+
+// Bytes that whole solves of this plan move with the kernels they run: the picked
+// ones where it has no schedule (on tiny grids the spectrum stays in LDS).
+double run_bytes(const fsp_plan_s* p) {
+  if (p->picked && tiny_supported(p)) {
+    const double n0 = p->n[0], n1 = p->n[1], n2 = p->n[2];
+    return (2 * n0 * n1 * n2 + (n0 + 1) * (n1 + 1) * (n2 + 1)) * p->rb;
+  }
+  return schedule_bytes(p, default_planes(p) ? PLANE_PAIRS : p->var);
 }
 
 }  // namespace
@@ -569,7 +581,7 @@ fsp_status fsp_plan_precompute_bytes(fsp_plan p, size_t* bytes) {
 
 fsp_status fsp_plan_model_bytes(fsp_plan p, double* bytes) {
   if (!p || !bytes) return fail(FSP_ERR_INVALID_ARG, "fsp_plan_model_bytes: NULL argument");
-  *bytes = model_bytes(p);
+  *bytes = schedule_bytes(p, p->var);
   return FSP_OK;
 }
 
@@ -917,10 +929,8 @@ static fsp::SolveGeom group_geom(const fsp_plan_s* p, const int* var);
 // plan whose kernels are picked take the plane kernels where those are the faster
 // for every number of items (default_planes), and one kernel on tiny grids.
 static fsp::SolveGeom group_geom(const fsp_plan_s* p, int first = 0, int last = 4) {
-  constexpr int P = fsp::PLANE;
-  constexpr int planes[5] = {P, P, 0, P, P};
   const bool whole = first == 0 && last == 4;
-  fsp::SolveGeom g = group_geom(p, whole && default_planes(p) ? planes : p->var);
+  fsp::SolveGeom g = group_geom(p, whole && default_planes(p) ? PLANE_PAIRS : p->var);
   g.tiny = whole && p->picked && tiny_supported(p);
   return g;
 }
@@ -1068,6 +1078,7 @@ hipError_t solve_items(fsp_plan geo, int count, const void* const* rho, void* co
 size_t work1_bytes(fsp_plan p) { return p->work1_bytes; }
 size_t ghat_bytes(fsp_plan p) { return p->ghat_bytes; }
 size_t precompute_bytes(fsp_plan p) { return p->pre_bytes; }
+double run_bytes(fsp_plan p) { return ::run_bytes(p); }
 const void* octant(fsp_plan p) { return static_cast<const char*>(p->ghat_read) + p->oct_off; }
 
 fsp_status bind_ghat(fsp_plan p, void* ghat_dev) {
@@ -1558,7 +1569,7 @@ struct fsp_batch_s {
   // Graph layout.  The leading groups (largest first) run in turn on
   // `branches` branches; the last `tail` groups (the smallest) then run
   // together on `tail_branches` branches, each group (largest first) put on
-  // the branch with the fewest model bytes so far, once the leading ones are
+  // the branch with the fewest bytes so far, once the leading ones are
   // done.  Measured on the 64-solve mix: the largest group alone first, then
   // the other four on three branches (0.792 ms; 0.798 on four, 0.802 on two,
   // 0.827 all in turn, 0.851 all five side by side).  Groups that overlap
@@ -1628,11 +1639,11 @@ hipError_t capture_batch(fsp_batch_s* b) {
     for (int i = 0; i < nb && e == hipSuccess; ++i) e = hipEventRecord(mid[i], side[i]);
     for (int t = 0; t < ntb && e == hipSuccess; ++t)
       for (int i = 0; i < nb && e == hipSuccess; ++i) e = hipStreamWaitEvent(side[nb + t], mid[i], 0);
-    // each (largest first) to the branch with the fewest model bytes so far
+    // each (largest first) to the branch with the fewest bytes so far
     std::vector<double> load(ntb, 0.0);
     for (int k = ng - nt; k < ng && e == hipSuccess; ++k) {
       const int t = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-      load[t] += model_bytes(b->groups[k].plan) * b->groups[k].count;
+      load[t] += run_bytes(b->groups[k].plan) * b->groups[k].count;
       launch_group(k, side[nb + t]);
     }
   }
@@ -1715,7 +1726,7 @@ fsp_status fsp_batch_create(int count, const fsp_plan* plans, const void* const*
     }
   // the group that moves the most bytes starts first, on the first branch
   std::stable_sort(b->groups.begin(), b->groups.end(), [](const fsp_batch_s::Group& x, const fsp_batch_s::Group& y) {
-    return model_bytes(x.plan) * x.count > model_bytes(y.plan) * y.count;
+    return run_bytes(x.plan) * x.count > run_bytes(y.plan) * y.count;
   });
   if (const char* env = std::getenv("FSP_BATCH_BRANCHES")) b->branches = std::max(1, std::min(16, std::atoi(env)));
   if (const char* env = std::getenv("FSP_BATCH_TAIL")) b->tail = std::max(0, std::min(8, std::atoi(env)));

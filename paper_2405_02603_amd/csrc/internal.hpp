@@ -21,7 +21,10 @@ hipError_t solve_items(fsp_plan geo, int count, const void* const* rho, void* co
 
 size_t work1_bytes(fsp_plan p);       // one spectrum's workspace
 size_t ghat_bytes(fsp_plan p);        // the Green's buffer
-size_t precompute_bytes(fsp_plan p);  // transient bytes of fsp_precompute
+size_t precompute_bytes(fsp_plan p);
+// Bytes that a whole solve moves with the kernels it runs; fsp_plan_model_bytes counts five passes
+// while the plan has no schedule.  Orders a batch's groups.
+double run_bytes(fsp_plan p);  // transient bytes of fsp_precompute
 const void* octant(fsp_plan p);       // the Green's octant of a precomputed plan
 
 // Bind only a (caller-owned) Green's buffer: the plan can be precomputed and its
