@@ -115,12 +115,14 @@ fsp_status fsp_plan_create(const fsp_plan_desc* desc, fsp_plan* out);
  * and 5). */
 fsp_status fsp_plan_bytes(fsp_plan p, size_t* ghat_bytes, size_t* work_bytes);
 
-/* Device bytes fsp_precompute needs transiently (freed before it returns to
- * the caller's stream order); reported for admission control.  This is the
- * pre-computation grid of Sections 2.3 and 2.4 in float64: (4N)^3 samples for
- * FSP_VICO, (2N+1)^3 for FSP_VICO_DCT (the memory reduction of Section 2.4),
- * (N+1)^3 for FSP_HOCKNEY, plus one intermediate of the per-axis transforms; at
- * most that (a potential on open axes, and FSP_HOCKNEY, never store that grid). */
+/* Device bytes fsp_precompute needs transiently (one allocation in stream
+ * order, freed before it returns to the caller's stream order); reported for
+ * admission control.  This is the pre-computation grid of Sections 2.3 and 2.4
+ * in float64: (4N)^3 samples for FSP_VICO, (2N+1)^3 for FSP_VICO_DCT (the memory
+ * reduction of Section 2.4), (N+1)^3 for FSP_HOCKNEY, plus one intermediate of
+ * the per-axis transforms and their matrices.  FSP_VICO_DCT on open axes without
+ * FSP_WANT_GRAD never stores that grid: (N+1)(2N+1)^2 values after the first
+ * axis, (N+1)^2 (2N+1) after the second (rows padded to 128 bytes). */
 fsp_status fsp_plan_precompute_bytes(fsp_plan p, size_t* bytes);
 
 /* Attach device memory.  ghat_dev / work_dev are caller-owned device buffers

@@ -449,6 +449,80 @@ static size_t image_elems(int nout, int kin, int period) {
   return (ke + 15) / 16 * ((re + 15) / 16 + (ro + 15) / 16) * 256;
 }
 
+// Whether the potential's transform is computed in three axis passes
+// (greens_axis.hpp): the Hockney-Eastwood kernel on any axes (its offsets fold
+// to the nearest image as they are sampled), the modified Vico-Greengard route
+// on open axes (a periodic axis folds the kernel between the two transforms
+// that the axis matrix merges).
+static bool by_axes(const fsp_plan_s* p) {
+  return p->d.greens == FSP_HOCKNEY || (p->d.greens == FSP_VICO_DCT && !p->periodic);
+}
+
+// Doubles of the matrix images that fsp_precompute uploads (the sizes
+// component_matrices builds): of every component that does not go by axes.
+static size_t matrix_elems(const fsp_plan_s* p) {
+  size_t cm = 0;
+  for (int comp = by_axes(p) ? 1 : 0; comp < (p->grad ? 4 : 1); ++comp)
+    for (int ax = 0; ax < 3; ++ax) {
+      const int m = p->n[ax];
+      const bool deriv = comp == ax + 1;
+      if (p->d.greens == FSP_VICO_DCT)
+        cm += deriv ? image_elems(m + 1, 2 * m + 1, 0) : image_elems(m + 1, 2 * m + 1, 2 * m);
+      else if (p->d.greens == FSP_VICO)
+        cm += image_elems(m + 1, 4 * m, 0);
+      cm += deriv ? image_elems(m + 1, m + 1, 0) : image_elems(m + 1, m + 1, m);
+    }
+  return cm;
+}
+
+// The transient buffer of fsp_precompute: two arrays A (at 0) and B that the
+// transforms go between, then the uploaded matrix images (`matrices` doubles) and
+// the axis passes' own.  Offsets in doubles.
+struct TransientLayout {
+  size_t b = 0, c = 0;
+  size_t image[3] = {0, 0, 0};  // axis passes: each axis's matrix image (equal axes share one)
+  size_t d1 = 0, p2 = 0;        // axis passes: inputs along axis 1, pitch of axis 2
+  size_t bytes = 0;
+};
+
+static TransientLayout transient_layout(const fsp_plan_s* p, size_t matrices) {
+  const size_t n0 = p->n[0], n1 = p->n[1], n2 = p->n[2];
+  const bool axes = by_axes(p), hockney = p->d.greens == FSP_HOCKNEY;
+  TransientLayout t;
+  // axis passes: Vico-Greengard's rows, of 2 n2 + 1 values, are padded to whole
+  // 128-byte lines (each array still fits where the (2n+1)^3 samples and their
+  // first transform are)
+  t.d1 = hockney ? n1 + 1 : 2 * n1 + 1;
+  t.p2 = hockney ? n2 + 1 : align_up(2 * n2 + 1, 16);
+  size_t a, b;
+  if (axes && !p->grad) {
+    a = (n0 + 1) * t.d1 * t.p2;
+    b = (n0 + 1) * (n1 + 1) * t.p2;
+  } else if (hockney) {
+    a = b = (n0 + 1) * (n1 + 1) * (n2 + 1);
+  } else if (p->d.greens == FSP_VICO_DCT) {
+    a = (2 * n0 + 1) * (2 * n1 + 1) * (2 * n2 + 1);
+    b = (2 * n1 + 1) * (2 * n2 + 1) * (n0 + 1);
+  } else {
+    a = 64 * n0 * n1 * n2;
+    b = 16 * n1 * n2 * (n0 + 1);
+  }
+  t.b = align_up(a, 32);
+  t.c = t.b + align_up(b, 32);
+  size_t end = t.c + matrices;
+  for (int i = 0; axes && i < 3; ++i) {
+    const int same = i > 0 && p->n[i] == p->n[0] ? 0 : i > 1 && p->n[i] == p->n[1] ? 1 : i;
+    if (same < i) {
+      t.image[i] = t.image[same];
+    } else {
+      t.image[i] = end;
+      end += fsp::green_axis_image_elems(p->n[i]);
+    }
+  }
+  t.bytes = align_up(end * 8, 256);
+  return t;
+}
+
 fsp_status fsp_plan_create(const fsp_plan_desc* desc, fsp_plan* out) {
   if (!desc || !out) return fail(FSP_ERR_INVALID_ARG, "fsp_plan_create: NULL argument");
   *out = nullptr;
@@ -537,30 +611,7 @@ fsp_status fsp_plan_create(const fsp_plan_desc* desc, fsp_plan* out) {
     delete p;
     return fail(FSP_ERR_UNSUPPORTED_SIZE, "fsp_plan_create: workspace plane offsets exceed 32 bits");
   }
-  // transient float64 precompute buffers (two ping-pong arrays) + cosine matrices
-  const size_t n0 = p->n[0], n1 = p->n[1], n2 = p->n[2];
-  size_t a = 0, b = 0;
-  if (d.greens == FSP_HOCKNEY) {
-    a = b = (n0 + 1) * (n1 + 1) * (n2 + 1);
-  } else if (d.greens == FSP_VICO_DCT) {
-    a = (2 * n0 + 1) * (2 * n1 + 1) * (2 * n2 + 1);
-    b = (2 * n1 + 1) * (2 * n2 + 1) * (n0 + 1);
-  } else {
-    a = 64 * n0 * n1 * n2;
-    b = 16 * n1 * n2 * (n0 + 1);
-  }
-  size_t cm = 0;  // matrix images of every component (the same sizes component_matrices builds)
-  for (int comp = 0; comp < (p->grad ? 4 : 1); ++comp)
-    for (int ax = 0; ax < 3; ++ax) {
-      const int m = p->n[ax];
-      const bool deriv = comp == ax + 1;
-      if (d.greens == FSP_VICO_DCT)
-        cm += deriv ? image_elems(m + 1, 2 * m + 1, 0) : image_elems(m + 1, 2 * m + 1, 2 * m);
-      else if (d.greens == FSP_VICO)
-        cm += image_elems(m + 1, 4 * m, 0);
-      cm += deriv ? image_elems(m + 1, m + 1, 0) : image_elems(m + 1, m + 1, m);
-    }
-  p->pre_bytes = align_up(a * 8, 256) + align_up(b * 8, 256) + align_up(cm * 8, 256);
+  p->pre_bytes = transient_layout(p, matrix_elems(p)).bytes;
   *out = p;
   g_err.clear();
   return FSP_OK;
@@ -765,15 +816,6 @@ static void component_matrices(const fsp_plan_s* p, int comp, std::vector<double
   }
 }
 
-// Whether the potential's transform is computed in three axis passes
-// (greens_axis.hpp): the Hockney-Eastwood kernel on any axes (its offsets fold
-// to the nearest image as they are sampled), the modified Vico-Greengard route
-// on open axes (a periodic axis folds the kernel between the two transforms
-// that the axis matrix merges).
-static bool by_axes(const fsp_plan_s* p) {
-  return p->d.greens == FSP_HOCKNEY || (p->d.greens == FSP_VICO_DCT && !p->periodic);
-}
-
 fsp_status fsp_precompute(fsp_plan p, void* stream) {
   if (!p) return fail(FSP_ERR_INVALID_ARG, "fsp_precompute: NULL plan");
   if (!p->bound) return fail(FSP_ERR_NOT_READY, "fsp_precompute: bind buffers first");
@@ -793,58 +835,28 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
   for (int c = first; c < ncomp; ++c) component_matrices(p, c, cm, ops);
   const size_t per_comp = ncomp > first ? ops.size() / (ncomp - first) : 0;
   const size_t n0 = n[0], n1 = n[1], n2 = n[2];
-  size_t a_elems, b_elems;
-  // axis passes: rows of the arrays between them; Vico-Greengard's, of 2 n2 + 1
-  // values, are padded to whole 128-byte lines (each array still fits where the
-  // (2n+1)^3 samples, here never stored, and their first transform would be)
-  const size_t d1 = gk == FSP_HOCKNEY ? n1 + 1 : 2 * n1 + 1;
-  const size_t p2 = gk == FSP_HOCKNEY ? n2 + 1 : align_up(2 * n2 + 1, 16);
-  if (axes && ncomp == 1) {
-    a_elems = (n0 + 1) * d1 * p2;
-    b_elems = (n0 + 1) * (n1 + 1) * p2;
-  } else if (gk == FSP_HOCKNEY) {
-    a_elems = b_elems = (n0 + 1) * (n1 + 1) * (n2 + 1);
-  } else if (gk == FSP_VICO_DCT) {
-    a_elems = (2 * n0 + 1) * (2 * n1 + 1) * (2 * n2 + 1);
-    b_elems = (2 * n1 + 1) * (2 * n2 + 1) * (n0 + 1);
-  } else {
-    a_elems = 64 * n0 * n1 * n2;
-    b_elems = 16 * n1 * n2 * (n0 + 1);
-  }
-  size_t c_elems = cm.size();
-  size_t image[3] = {0, 0, 0};  // axis passes: each axis's matrix image in C (equal axes share one)
-  if (axes)
-    for (int a = 0; a < 3; ++a) {
-      const int same = a > 0 && n[a] == n[0] ? 0 : a > 1 && n[a] == n[1] ? 1 : a;
-      if (same < a) {
-        image[a] = image[same];
-      } else {
-        image[a] = c_elems;
-        c_elems += fsp::green_axis_image_elems(n[a]);
-      }
-    }
-  // one transient buffer: A, B and the matrices
-  const size_t a_off = 0, b_off = align_up(a_elems, 32), c_off = b_off + align_up(b_elems, 32);
+  // one transient buffer: the arrays and the matrices
+  const TransientLayout lay = transient_layout(p, cm.size());
   double* T = nullptr;
-  e = hipMallocAsync((void**)&T, (c_off + c_elems) * 8, s);
+  e = hipMallocAsync((void**)&T, lay.bytes, s);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(FSP_ERR_OUT_OF_MEMORY, "fsp_precompute: transient float64 buffers could not be allocated");
   }
-  double *const A = T + a_off, *const B = T + b_off, *const C = T + c_off;
+  double *const A = T, *const B = T + lay.b, *const C = T + lay.c;
   p->ready = false;
   if (!cm.empty()) e = hipMemcpyAsync(C, cm.data(), cm.size() * 8, hipMemcpyHostToDevice, s);
   if (axes && e == hipSuccess) {
     const bool vico = gk == FSP_VICO_DCT;
     for (int a = 0; a < 3 && e == hipSuccess; ++a)
-      if ((a == 0 || image[a] != image[0]) && (a < 2 || image[a] != image[1]))
-        e = fsp::green_axis_image(C + image[a], n[a], vico, s);
+      if ((a == 0 || lay.image[a] != lay.image[0]) && (a < 2 || lay.image[a] != lay.image[1]))
+        e = fsp::green_axis_image(T + lay.image[a], n[a], vico, s);
     fsp::AxisArgs g{};
     g.n0 = n[0];
     g.n1 = n[1];
     g.n2 = n[2];
-    g.d1 = (int)d1;
-    g.p2 = (int)p2;
+    g.d1 = (int)lay.d1;
+    g.p2 = (int)lay.p2;
     g.octant = static_cast<char*>(p->ghat) + p->oct_off;
     g.tile = p->gtile;
     g.f64 = p->d.prec == FSP_F64;
@@ -859,7 +871,7 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
     double* out[3] = {A, B, nullptr};
     const int cols[3] = {g.d1 * g.p2, (n[0] + 1) * g.p2, (n[0] + 1) * (n[1] + 1)};
     for (int a = 0; a < 3 && e == hipSuccess; ++a) {
-      g.image = C + image[a];
+      g.image = T + lay.image[a];
       g.x = in[a];
       g.y = out[a];
       g.n = n[a];
