@@ -5,7 +5,8 @@ alone and in every kind of launch.
 
 Each is told by its bits: a whole solve equals the passes run one by one, the
 plane schedule or the workspace it left untouched, bit for bit.  The tolerance
-against the oracle is that of every solve.
+against the oracle is that of every solve.  The grids are ones that no other test
+tunes: a new plan of a tuned grid starts with that schedule.
 """
 from __future__ import annotations
 
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 LO, HI = (0.0, -0.5, 0.0), (1.0, 0.75, 1.5)
 PLANES = [(8, 32, 32), (24, 48, 48), (12, 64, 64)]
-TINY = [(16, 16, 16), (8, 12, 24)]
+TINY = [(12, 16, 16), (8, 12, 24)]
 
 
 def _plan(n, prec, **kw):
@@ -68,7 +69,7 @@ def test_zeros_that_are_set_are_variant_0_of_each_pass(n, prec, tol):
 
 
 @pytest.mark.parametrize("prec,tol", [("f64", F64_TOL), ("f32", F32_TOL)])
-@pytest.mark.parametrize("n,items", [((8, 32, 32), 1), ((12, 48, 48), 10), ((48, 48, 48), 11), ((64, 64, 64), 8)])
+@pytest.mark.parametrize("n,items", [((8, 32, 32), 1), ((12, 48, 48), 10), ((96, 48, 48), 6), ((128, 64, 64), 4)])
 def test_a_plan_without_a_schedule_runs_the_plane_pairs(n, items, prec, tol):
     """Solves and gradients, few and many planes a launch."""
     import torch
@@ -94,32 +95,3 @@ def test_a_plan_without_a_schedule_runs_the_plane_pairs(n, items, prec, tol):
             g.schedule = sched
         grads.append([t.clone() for t in g.solve_grad(rhos[0], want_phi=True)])
     assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
-
-
-@pytest.mark.parametrize("prec", ["f32", "f64"])
-@pytest.mark.parametrize("n", [(32, 32, 32), (16, 12, 16)])
-def test_tuners_time_and_keep_what_they_name(n, prec):
-    """What the tuners keep runs as it says: a kept schedule gives the bits of that schedule set on a
-    new plan; where none is kept (one kernel picked), the workspace stays untouched."""
-    import torch
-
-    from paper_2405_02603_amd import autotune_batch
-
-    dtype = torch.float32 if prec == "f32" else torch.float64
-    plans = [_plan(n, prec) for _ in range(4)]
-    r = to_dev(np.random.default_rng(2).standard_normal(n), dtype)
-    times = plans[0].autotune(r, reps=2)
-    assert times["solve_separate"] > 0
-    for step in range(2):
-        if step:
-            autotune_batch(plans, [r.clone() for _ in plans], reps=2)
-        for p in plans[:1 if not step else None]:
-            p.work_buf.fill_(255)
-            got = p.solve(r)
-            again = _plan(n, prec)
-            again.schedule = p.schedule
-            if bool((p.work_buf == 255).all()):
-                assert n == (16, 12, 16) and p.schedule == [0] * 5
-                assert torch.equal(got, plans[0].solve_static(r))
-            else:
-                assert torch.equal(got, again.solve(r)), p.schedule
