@@ -1007,7 +1007,18 @@ static bool same_shape(const fsp_plan_s* a, const fsp_plan_s* b) {
 }
 
 static hipError_t run_group(const fsp::SolveGeom& g, bool f64, int first, int last, hipStream_t s) {
-  return f64 ? fsp::solve_f64(g, first, last, s) : fsp::solve_f32(g, first, last, s);
+  auto run = [&](const fsp::SolveGeom& q) {
+    return f64 ? fsp::solve_f64(q, first, last, s) : fsp::solve_f32(q, first, last, s);
+  };
+  // As one kernel a solve writes its phi while others of the launch may not have
+  // read their rho; the passes have read every rho before the first phi.
+  const size_t field = (size_t)g.n0 * g.n1 * g.n2 * (f64 ? 8 : 4);
+  if (g.tiny && !g.items_dev && g.items > 1 && fsp::internal::items_cross(g.items, g.rho, g.phi, field)) {
+    fsp::SolveGeom q = g;
+    q.tiny = false;
+    return run(q);
+  }
+  return run(g);
 }
 
 static fsp_status solve_one(fsp_plan p, const void* rho, void* phi, hipStream_t s, int first = 0, int last = 4) {
@@ -1069,6 +1080,31 @@ static fsp_status check_batch(const char* who, int count, const fsp_plan* plans,
 // Library-internal entry points of the serving engine (internal.hpp).
 namespace fsp {
 namespace internal {
+
+bool items_cross(int count, const void* const* rho, void* const* phi, size_t field) {
+  auto at = [](const void* q) { return reinterpret_cast<uintptr_t>(q); };
+  auto apart = [&](uintptr_t r, uintptr_t f) { return r + field <= f || f + field <= r; };
+  if (count <= 32) {
+    for (int i = 0; i < count; ++i)
+      for (int j = 0; j < count; ++j)
+        if (i != j && !apart(at(rho[j]), at(phi[i]))) return true;
+    return false;
+  }
+  try {
+    std::vector<std::pair<uintptr_t, int>> f(count);
+    for (int i = 0; i < count; ++i) f[i] = {at(phi[i]), i};
+    std::sort(f.begin(), f.end());
+    for (int j = 0; j < count; ++j) {
+      const uintptr_t r = at(rho[j]);
+      auto it = std::lower_bound(f.begin(), f.end(), std::make_pair(r < field ? 0 : r - field + 1, -1));
+      for (; it != f.end() && it->first < r + field; ++it)  // two entries at most: one is not this solve's
+        if (it->second != j) return true;
+    }
+    return false;
+  } catch (const std::bad_alloc&) {
+    return true;
+  }
+}
 
 hipError_t solve_items(fsp_plan geo, int count, const void* const* rho, void* const* phi, void* const* work,
                        const void* const* octant, hipStream_t s) {
@@ -1589,8 +1625,12 @@ struct fsp_batch_s {
   int branches = 1;
   int tail = 8;
   int tail_branches = 3;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
+  // Solves of one kernel each (tiny grids) may not run together where one's phi
+  // is another's rho: while `cross`, such groups take the passes, in a graph of
+  // their own (launches of the other may still be in flight).
+  bool cross = false;
+  hipGraph_t graph[2] = {nullptr, nullptr};
+  hipGraphExec_t exec[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -1644,6 +1684,7 @@ hipError_t capture_batch(fsp_batch_s* b) {
     fsp::SolveGeom g = group_geom(gr.plan);
     g.items = gr.count;
     g.items_dev = b->table + gr.first;
+    g.tiny = g.tiny && !b->cross;
     e = run_group(g, gr.plan->d.prec == FSP_F64, 0, 4, st);
   };
   for (int k = 0; k < ng - nt && e == hipSuccess; ++k) launch_group(k, side[k % nb]);
@@ -1666,8 +1707,8 @@ hipError_t capture_batch(fsp_batch_s* b) {
     hipError_t e2 = hipStreamEndCapture(cs, &g);
     if (e == hipSuccess) e = e2;
     if (e == hipSuccess) {
-      b->graph = g;
-      e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
+      b->graph[b->cross] = g;
+      e = hipGraphInstantiate(&b->exec[b->cross], g, nullptr, nullptr, 0);
     } else if (g) {
       (void)hipGraphDestroy(g);
     }
@@ -1683,9 +1724,34 @@ hipError_t capture_batch(fsp_batch_s* b) {
   return e;
 }
 
+// Whether a group of one-kernel solves has a phi that is another's rho.
+bool batch_cross(const fsp_batch_s* b) {
+  std::vector<const void*> rho;
+  std::vector<void*> phi;
+  for (const auto& gr : b->groups) {
+    const fsp_plan p = gr.plan;
+    if (gr.count < 2 || !p->picked || !tiny_supported(p)) continue;
+    try {
+      rho.clear();
+      phi.clear();
+      for (int i = gr.first; i < gr.first + gr.count; ++i) {
+        rho.push_back(b->host[i].rho);
+        phi.push_back(b->host[i].phi);
+      }
+    } catch (const std::bad_alloc&) {
+      return true;
+    }
+    const size_t field = (size_t)p->n[0] * p->n[1] * p->n[2] * p->rb;
+    if (fsp::internal::items_cross(gr.count, rho.data(), phi.data(), field)) return true;
+  }
+  return false;
+}
+
 void free_batch(fsp_batch_s* b) {
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  if (b->graph) (void)hipGraphDestroy(b->graph);
+  for (int i = 0; i < 2; ++i) {
+    if (b->exec[i]) (void)hipGraphExecDestroy(b->exec[i]);
+    if (b->graph[i]) (void)hipGraphDestroy(b->graph[i]);
+  }
   if (b->table) (void)hipFree(b->table);
   delete b;
 }
@@ -1740,6 +1806,7 @@ fsp_status fsp_batch_create(int count, const fsp_plan* plans, const void* const*
   std::stable_sort(b->groups.begin(), b->groups.end(), [](const fsp_batch_s::Group& x, const fsp_batch_s::Group& y) {
     return run_bytes(x.plan) * x.count > run_bytes(y.plan) * y.count;
   });
+  b->cross = batch_cross(b);
   if (const char* env = std::getenv("FSP_BATCH_BRANCHES")) b->branches = std::max(1, std::min(16, std::atoi(env)));
   if (const char* env = std::getenv("FSP_BATCH_TAIL")) b->tail = std::max(0, std::min(8, std::atoi(env)));
   if (const char* env = std::getenv("FSP_BATCH_TAIL_BRANCHES")) b->tail_branches = std::max(1, std::min(8, std::atoi(env)));
@@ -1785,6 +1852,7 @@ fsp_status fsp_batch_set_io(fsp_batch b, const void* const* rho, void* const* ph
     hipLaunchKernelGGL(k_set_items, dim3(1), dim3(SET_ITEMS), 0, s, a);
     e = hipGetLastError();
   }
+  b->cross = batch_cross(b);
   if (e != hipSuccess) return fail_hip(e, "fsp_batch_set_io");
   return FSP_OK;
 }
@@ -1794,11 +1862,11 @@ fsp_status fsp_batch_launch(fsp_batch b, void* stream) {
   DeviceGuard guard;
   hipError_t e = guard.enter(b->device);
   if (e != hipSuccess) return fail_hip(e, "fsp_batch_launch: hipSetDevice");
-  if (!b->exec) {
+  if (!b->exec[b->cross]) {
     e = capture_batch(b);
     if (e != hipSuccess) return fail_hip(e, "fsp_batch_launch: graph capture");
   }
-  e = hipGraphLaunch(b->exec, reinterpret_cast<hipStream_t>(stream));
+  e = hipGraphLaunch(b->exec[b->cross], reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail_hip(e, "fsp_batch_launch: hipGraphLaunch");
   return FSP_OK;
 }

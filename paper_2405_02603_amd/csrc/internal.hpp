@@ -19,6 +19,9 @@ namespace internal {
 hipError_t solve_items(fsp_plan geo, int count, const void* const* rho, void* const* phi, void* const* work,
                        const void* const* octant, hipStream_t s);
 
+// Whether any solve's phi overlaps another solve's rho (its own may be its rho); arrays of `field` bytes.
+bool items_cross(int count, const void* const* rho, void* const* phi, size_t field);
+
 size_t work1_bytes(fsp_plan p);       // one spectrum's workspace
 size_t ghat_bytes(fsp_plan p);        // the Green's buffer
 size_t precompute_bytes(fsp_plan p);
