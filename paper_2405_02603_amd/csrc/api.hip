@@ -914,7 +914,7 @@ fsp_status fsp_precompute(fsp_plan p, void* stream) {
       dims[1] = samples[1];
       dims[2] = samples[2];
       for (int a = 0; a < 3; ++a) contract(n[a] + 1);
-    // inverse transform on the 4n grid: 1 / prod(4 n_d h_d) = 1 / (64 n0 n1 n2 V)
+      // inverse transform on the 4n grid: 1 / prod(4 n_d h_d) = 1 / (64 n0 n1 n2 V)
       scale /= 64.0 * n0 * n1 * n2 * p->V;
     }
     if (p->periodic && e == hipSuccess) {  // the kernel octant (in X) folded to the nearest image

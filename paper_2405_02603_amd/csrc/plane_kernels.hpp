@@ -100,7 +100,7 @@ __host__ __device__ constexpr PlaneCfg plane_few_cfg(int N) {
 }
 
 // One column tile: the inverse kernel takes two planes of LDS, and whole solves
-// on the default variants run as plane kernels.
+// of plans without a schedule run as plane kernels.
 __host__ __device__ constexpr bool plane_wide(int N, const PlaneCfg& c) { return c.tc == N; }
 template <typename T>
 __host__ __device__ constexpr bool plane_default(int N) {

@@ -141,13 +141,14 @@ __device__ __forceinline__ cx<T> ld_once(const cx<T>* p) {
 // to what is; where the spectra S of a launch group fit in it, streaming them
 // throws that away.  Measured (us; whole solves or batched steps, cached ->
 // streamed):
-//   Always: the loads of rho, the stores of the axis-0 pass and of phi.
+//   Always: the stores of the axis-0 pass and of phi, and the loads of rho (the
+//     plane kernels': from 200 MB, see there).
 //   Never: the axis-1 passes' loads and the inverse axis-1 pass's stores (read
 //     next by the row pass: 256^3 float64 P4 + P5 222 -> 211 since cached).
 //   By the total of the group's S (StreamBits, set by the launcher):
-//     the axis-1 forward stores, from 200 MB: 256^3 float32 385 -> 370, sixteen
-//       128^3 833 -> 756, 512^3 float32 3553 -> 3442; below, 128^3 62.4 -> 63.3,
-//       192^3 float32 (123 MB) 172.8 -> 176.0.
+//     the axis-1 forward stores (and the forward plane kernel's), from 200 MB:
+//       256^3 float32 385 -> 370, sixteen 128^3 833 -> 756, 512^3 float32 3553 ->
+//       3442; below, 128^3 62.4 -> 63.3, 192^3 float32 (123 MB) 172.8 -> 176.0.
 //     the inverse row loads, from 100 MB: 256^3 float64 P5 93 -> 75; below,
 //       128^3 62.4 -> 64.1, two 128^3 102.8 -> 106.5.
 //     the float64 forward row stores, from 600 MB (the half of S they write is

@@ -1,7 +1,7 @@
-"""Default solves of n x 32 x 32, 48 x 48 and 64 x 64 grids run as plane kernels:
-each shape (two blocks a plane, wide, narrow) at the ends of its range of planes
-a launch, against the oracle, for random data and for data that lives in the two
-columns that share a transform (k2 = 0 and k2 = n2).
+"""Solves of n x 32 x 32, 48 x 48 and 64 x 64 grids by variant 0 of each pass, in
+launches of as many planes as lie at the ends of the plane kernels' ranges (those
+kernels: test_gpu_picked_kernels.py), against the oracle, for random data and for
+data that lives in the columns k2 = 0 and k2 = n2.
 
 Tolerances are those of every solve: 1e-12 (float64) and 1e-6 (float32) of the
 norm, six times that of the RMS per element.

@@ -13,7 +13,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
-from gpu_util import F32_TOL, F64_TOL, reference, rel_l2, to_dev, to_host
+from gpu_util import F32_ELEM, F32_TOL, F64_ELEM, F64_TOL, elem_err, reference, rel_l2, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -95,3 +95,34 @@ def test_a_plan_without_a_schedule_runs_the_plane_pairs(n, items, prec, tol):
             g.schedule = sched
         grads.append([t.clone() for t in g.solve_grad(rhos[0], want_phi=True)])
     assert torch.equal(grads[0][0], grads[1][0]) and torch.equal(grads[0][1], grads[1][1])
+
+
+@pytest.mark.parametrize("prec,tol,etol", [("f64", F64_TOL, F64_ELEM), ("f32", F32_TOL, F32_ELEM)])
+@pytest.mark.parametrize("n12", [32, 48, 64])
+@pytest.mark.parametrize("n0,items", [(8, 1), (12, 10), (64, 8), (48, 11), (96, 6)])
+def test_plane_shapes_against_the_oracle(n0, items, n12, prec, tol, etol):
+    """Both shapes at 48 points (the second from 513 planes a launch on), and the one at 32 and 64,
+    for random data and for data that lives in the two columns that share a transform (k2 = 0 and
+    k2 = n2)."""
+    import torch
+
+    from paper_2405_02603_amd import _lib, solve_batched
+
+    P = _lib.PLANE
+    dtype = torch.float32 if prec == "f32" else torch.float64
+    n = (n0, n12, n12)
+    rng = np.random.default_rng(n0 * 100 + n12 + 1)
+    plans = [_plan(n, prec) for _ in range(items)]
+    for p in plans:
+        p.schedule = [P, P, 0, P, P]
+    rhos = [to_dev(rng.standard_normal(n), dtype) for _ in plans]
+    rhos[-1] = to_dev(1.0 + (-1.0) ** np.arange(n12) * rng.standard_normal(n[:2])[:, :, None], dtype)
+    for p in plans:
+        p.work_buf.fill_(255)
+    outs = solve_batched(plans, rhos)
+    for i in {0, items // 2, items - 1}:
+        ref = reference(to_host(rhos[i]), "hockney", LO, HI)
+        assert rel_l2(to_host(outs[i]), ref) <= tol, i
+        assert elem_err(to_host(outs[i]), ref) <= etol, i
+    r = rhos[0].clone()
+    assert torch.equal(plans[0].solve(r, out=r), plans[0].solve(rhos[0]))  # in place
