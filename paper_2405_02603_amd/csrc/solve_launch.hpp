@@ -173,21 +173,21 @@ __host__ __device__ constexpr TileCfg conv_cfg(int L, int v) {
   X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024)
 #define FSP_VARIANTS(X, LV) X(LV, 0) X(LV, 1) X(LV, 2)
 
-template <typename T>
+// STREAM: float64 rows below 384 with streamed stores, in a translation unit of
+// their own (beside the others they moved the small grids' kernels: 48x192x96
+// 55.7 -> 56.1 us).
+template <typename T, bool STREAM>
 hipError_t launch_p1(int LC, int v, const RowArgs& a, int items, hipStream_t s) {
   bool found = false;
 #define FSP_CASE_V(LV, VV)                                                                          \
   if (LC == LV && v == VV) {                                                                        \
     constexpr TileCfg c = row_cfg<T>(LV, VV);                                                       \
     const int blocks = (a.nrows + c.tiles * c.groups - 1) / (c.tiles * c.groups);                   \
-    constexpr bool always = stream_row_store(LV), by_size = sizeof(T) == 8 && !always;              \
-    if (by_size && (a.stream & STREAM_ROW_STORE))                                                   \
-      hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups, always || by_size>),     \
+    if constexpr (!STREAM || !stream_row_store(LV)) {                                               \
+      hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups, STREAM || stream_row_store(LV)>), \
                          dim3(blocks, items), dim3(c.tiles * c.nq), 0, s, a);                       \
-    else                                                                                            \
-      hipLaunchKernelGGL((k_row_r2c<T, LV, c.pid, c.tiles, c.nq, c.groups, always>),                \
-                         dim3(blocks, items), dim3(c.tiles * c.nq), 0, s, a);                       \
-    found = true;                                                                                   \
+      found = true;                                                                                 \
+    }                                                                                               \
   }
 #define FSP_CASE(LV) FSP_VARIANTS(FSP_CASE_V, LV)
   FSP_ROW_LENGTHS(FSP_CASE)
@@ -392,10 +392,11 @@ hipError_t launch_slab(int L, const SlabArgs& a, int items, hipStream_t s) {
 #ifdef FSP_SPLIT_LAUNCHERS
 // The launchers are instantiated in their own translation units (compiled in
 // parallel); the solve driver only references them.
-extern template hipError_t launch_p1<float>(int, int, const RowArgs&, int, hipStream_t);
+extern template hipError_t launch_p1<float, false>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_p5<float>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_col<float>(int, int, int, const ColArgs&, int, hipStream_t);
-extern template hipError_t launch_p1<double>(int, int, const RowArgs&, int, hipStream_t);
+extern template hipError_t launch_p1<double, false>(int, int, const RowArgs&, int, hipStream_t);
+extern template hipError_t launch_p1<double, true>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_p5<double>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_col<double>(int, int, int, const ColArgs&, int, hipStream_t);
 extern template hipError_t launch_slab<float>(int, const SlabArgs&, int, hipStream_t);
@@ -558,7 +559,9 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
           ra.out[i] = g.work[i];
         }
         ra.tw = g.tw_row[0];
-        return launch_p1<T>(g.n2, g.var[0], ra, g.items, s);
+        if constexpr (sizeof(T) == 8)
+          if ((stream & STREAM_ROW_STORE) && !stream_row_store(g.n2)) return launch_p1<T, true>(g.n2, g.var[0], ra, g.items, s);
+        return launch_p1<T, false>(g.n2, g.var[0], ra, g.items, s);
       case 1:
         set_cols(ca, tc2, c0, c1);
         ca.tw = g.tw_c1[1];

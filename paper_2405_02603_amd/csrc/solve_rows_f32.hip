@@ -2,6 +2,6 @@
 #include "solve_launch.hpp"
 
 namespace fsp {
-template hipError_t launch_p1<float>(int, int, const RowArgs&, int, hipStream_t);
+template hipError_t launch_p1<float, false>(int, int, const RowArgs&, int, hipStream_t);
 template hipError_t launch_p5<float>(int, int, const RowArgs&, int, hipStream_t);
 }  // namespace fsp
