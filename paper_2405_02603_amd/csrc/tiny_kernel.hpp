@@ -14,7 +14,8 @@
 // float32 23.9 -> 11.5, 12x16x24 float32 23.7 -> 10.8, 16x16x32 float32 23.8 ->
 // 18.2, 16^3 float64 23.8 -> 16.1; a batch of 64 16^3 127 -> 80.  What bounds it:
 // the latency of one block's five passes; at 16^3 in float64 the 544 axis-0
-// pencils take the 512 threads a second, nearly empty, round.
+// pencils take the 512 threads a second, nearly empty, round, and a 32-point
+// pencil's registers spill 80 bytes a lane.
 #pragma once
 
 #include "solve_kernels.hpp"
