@@ -143,8 +143,9 @@ __device__ __forceinline__ cx<T> ld_once(const cx<T>* p) {
 // streamed):
 //   Always: the stores of the axis-0 pass and of phi, and the loads of rho (the
 //     plane kernels': from 200 MB, see there).
-//   Never: the axis-1 passes' loads and the inverse axis-1 pass's stores (read
-//     next by the row pass: 256^3 float64 P4 + P5 222 -> 211 since cached).
+//   Never: the axis-1 passes' loads and, but for small float64 groups (below), the
+//     inverse axis-1 pass's stores (read next by the row pass: 256^3 float64 P4 + P5
+//     222 -> 211 since cached).
 //   By the total of the group's S (StreamBits, set by the launcher):
 //     the axis-1 forward stores (and the forward plane kernel's), from 200 MB:
 //       256^3 float32 385 -> 370, sixteen 128^3 833 -> 756, 512^3 float32 3553 ->
@@ -155,6 +156,11 @@ __device__ __forceinline__ cx<T> ld_once(const cx<T>* p) {
 //       then beyond the cache): float64 sixteen 128^3 1498 -> 1445, three
 //       192^3 976 -> 960; equal at 540 MB (eight 128^3, one 256^3), below, four
 //       128^3 333 -> 338, 192^3 323 -> 330.
+//     in float64 all of these and the inverse axis-1 stores, up to 32 MB (all
+//       L2s together; a pass then hands on little that its end has to write
+//       back): 48x192x96 63.6 -> 59.5, 64x96x96 52.0 -> 49.2, 32x32x512 46.8 ->
+//       43.6, twenty-four 32x24x32 51.2 -> 47.2; past it, 128^3 103.6 -> 109.0,
+//       eight 64x32x96 (55 MB) 82.1 -> 85.7.
 //   By type and length:
 //     the forward row stores, rows of 384 and more: 512^3 float32 P1 + P2
 //       1035 -> 986; 256^3 float32 122 -> 135.
@@ -169,6 +175,7 @@ enum StreamBits {
 constexpr long long STREAM_COL_STORE_MIN = 200000000;  // bytes of S in the launch group
 constexpr long long STREAM_ROW_LOAD_MIN = 100000000;
 constexpr long long STREAM_ROW_STORE_MIN = 600000000;
+constexpr long long STREAM_ALL_MAX = 32000000;
 
 __host__ __device__ constexpr bool stream_row_store(int n2) { return n2 >= 384; }
 template <typename T>
@@ -224,7 +231,9 @@ __device__ __forceinline__ void place_column(const ColArgs& a, int c, int& col, 
 }
 
 // ----------------------------------------------------------------- P2 / P4
-template <typename T, int L, int PID, int TC, int NQ, bool INV>
+// STREAM: the inverse pass's results are streamed past the caches (the forward
+// pass's by StreamBits).
+template <typename T, int L, int PID, int TC, int NQ, bool INV, bool STREAM = false>
 __global__ __launch_bounds__(TC* NQ) void k_col_fft(ColArgs a) {
   constexpr int K = plan_len(L, PID);
   __shared__ cx<T> lds[K > 1 ? L * TC : 1];
@@ -261,10 +270,9 @@ __global__ __launch_bounds__(TC* NQ) void k_col_fft(ColArgs a) {
     else
       dft_half_in<F::R, false, T>(v[j]);
   }
-  // the inverse pass's results are read next while in the memory-side cache
   auto store = [&](auto f) {
     if constexpr (INV)
-      f(std::false_type{});
+      f(std::bool_constant<STREAM>{});
     else
       by_stream(a.stream & STREAM_COL_STORE, f);
   };

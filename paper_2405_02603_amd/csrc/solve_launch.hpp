@@ -346,6 +346,25 @@ hipError_t launch_col(int L, int v, int kind, const ColArgs& a, int items, hipSt
   return hipGetLastError();
 }
 
+// The inverse axis-1 pass (P4) with streamed stores, in a translation unit of its own as above.
+template <typename T>
+hipError_t launch_p4_stream(int L, int v, const ColArgs& a, int items, hipStream_t s) {
+  bool found = false;
+#define FSP_CASE_V(LV, VV)                                                                          \
+  if (L == LV && v == VV) {                                                                         \
+    constexpr TileCfg c = col_cfg<T>(LV, VV);                                                       \
+    hipLaunchKernelGGL((k_col_fft<T, LV, c.pid, c.tiles, c.nq, true, true>),                        \
+                       dim3((unsigned)(a.nouter * a.ntiles), (unsigned)items), dim3(c.tiles * c.nq), 0, s, a); \
+    found = true;                                                                                   \
+  }
+#define FSP_CASE(LV) FSP_VARIANTS(FSP_CASE_V, LV)
+  FSP_COL_LENGTHS(FSP_CASE)
+#undef FSP_CASE
+#undef FSP_CASE_V
+  if (!found) return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 // Fused axis-1 / axis-0 / axis-1 schedule for small cubic grids (n0 == n1):
 // one block per TC columns holds the (i0, k1) slab in LDS.  tiles == 0 means
 // unsupported.  LDS = (n N TC + groups TC 2n) sizeof(cx<T>) <= 160 KB.
@@ -397,6 +416,7 @@ extern template hipError_t launch_p5<float>(int, int, const RowArgs&, int, hipSt
 extern template hipError_t launch_col<float>(int, int, int, const ColArgs&, int, hipStream_t);
 extern template hipError_t launch_p1<double, false>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_p1<double, true>(int, int, const RowArgs&, int, hipStream_t);
+extern template hipError_t launch_p4_stream<double>(int, int, const ColArgs&, int, hipStream_t);
 extern template hipError_t launch_p5<double>(int, int, const RowArgs&, int, hipStream_t);
 extern template hipError_t launch_col<double>(int, int, int, const ColArgs&, int, hipStream_t);
 extern template hipError_t launch_slab<float>(int, const SlabArgs&, int, hipStream_t);
@@ -470,9 +490,11 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   // gradient's forward passes write one)
   const long long s_one = (long long)g.n0 * plane * (long long)sizeof(cx<T>);
   const long long s_bytes = (g.nout ? g.nout : g.items) * s_one;
-  const int stream = (s_bytes >= STREAM_COL_STORE_MIN ? STREAM_COL_STORE : 0) |
-                     (s_bytes >= STREAM_ROW_LOAD_MIN ? STREAM_ROW_LOAD : 0) |
-                     (g.items * s_one >= STREAM_ROW_STORE_MIN ? STREAM_ROW_STORE : 0);
+  const bool small = sizeof(T) == 8 && s_bytes <= STREAM_ALL_MAX;
+  const int plane_stream = s_bytes >= STREAM_COL_STORE_MIN ? STREAM_COL_STORE : 0;
+  const int stream = plane_stream | (small ? STREAM_COL_STORE : 0) |
+                     (small || s_bytes >= STREAM_ROW_LOAD_MIN ? STREAM_ROW_LOAD : 0) |
+                     (small || g.items * s_one >= STREAM_ROW_STORE_MIN ? STREAM_ROW_STORE : 0);
   RowArgs ra{};
   ra.items = g.items_dev;
   ra.stream = stream;
@@ -531,7 +553,7 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
   const bool plane_fwd = g.var[0] == PLANE, plane_inv = g.var[3] == PLANE;
   PlaneArgs pa{};
   pa.items = g.items_dev;
-  pa.stream = stream;
+  pa.stream = plane_stream;
   pa.plane = plane;
   pa.pitch = g.pitch;
   auto run = [&](int pass, int c0, int c1) -> hipError_t {
@@ -586,6 +608,8 @@ hipError_t launch_solve(const SolveGeom& g, int first, int last, hipStream_t s) 
         for (int i = 0; i < (tab ? 0 : npost); ++i) c4.data[i] = after[i];
         set_cols(c4, tc4, c0, c1);
         c4.tw = g.tw_c1[3];
+        if constexpr (sizeof(T) == 8)
+          if (small) return launch_p4_stream<T>(2 * g.n1, g.var[3], c4, npost, s);
         return launch_col<T>(2 * g.n1, g.var[3], 1, c4, npost, s);
       }
       case 4:
