@@ -265,19 +265,36 @@ inline ColArgs conv_gather(const ColArgs& a, int tc) {
   return b;
 }
 
+// Blocks of a kernel that the GPU holds at once (256 compute units).
+template <auto* KERNEL>
+int resident_blocks(int threads) {
+  static const int n = [threads] {
+    int cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&cu, KERNEL, threads, 0) != hipSuccess) (void)hipGetLastError();
+    return 256 * (cu > 0 ? cu : 1);
+  }();
+  return n;
+}
+
 // A block's two pencil sets (k1 and 2 n1 - k1) run one after the other, which
-// halves the reads of the octant; on a grid of fewer than CONV_SINGLE_BLOCKS
-// blocks (four a CU) that chain is what the pass waits for, and each set gets
-// a block of its own.  Whole solves, paired / single: 48^3 f64 28.8 / 27.3 us,
-// 64^3 f64 36.9 / 34.0, 64^3 f32 27.6 / 25.1, 96^3 f64 61.2 / 59.6, 96^3 f32
-// 40.4 / 39.3, 256x64x64 f32 48.2 / 45.5; on larger launches it loses: 48x192x96
-// f64 (1261 blocks) 56.3 / 57.1, nineteen 32^3 f32 in a batch (1254) 39.9 / 41.5,
-// six 96^3 f32 (2328) 133.8 / 138.3.  Grids whose lone column is gathered are
-// larger still.
+// halves the reads of the octant; on a small grid that chain is what the pass
+// waits for, and each set gets a block of its own.  That pays where it takes
+// fewer rounds of resident blocks, a round of two sets counting double: not
+// where two sets a block fill the GPU once and one set a block does not fit.
+// Measured over 130 shapes of 200 to 1023 blocks: one set a block always /
+// where it takes fewer rounds: 0.984 / 0.978 of two sets' time, the worst 1.12
+// (256x64x48 f64, 455 blocks on 512 places: 57.4 / 64.3 us) / 1.04.  Whole
+// solves, two / one: 48^3 f64 28.8 / 27.3 us, 64^3 f64 36.9 / 34.0, 64^3 f32
+// 27.6 / 25.1, 128x128x24 f32 36.9 / 34.7.  From CONV_SINGLE_BLOCKS on it
+// loses: 48x192x96 f64 (1351 blocks) 56.3 / 57.1, nineteen 32^3 f32 in a batch
+// (1254) 39.9 / 41.5, six 96^3 f32 (4074) 133.8 / 138.3.  Grids whose lone
+// column is gathered are larger still.
 constexpr long long CONV_SINGLE_BLOCKS = 1024;
-inline ColArgs conv_single(const ColArgs& a, int items) {
+inline ColArgs conv_single(const ColArgs& a, int items, int resident) {
   ColArgs b = a;
-  if (b.ntail == 0 && (long long)b.nouter * b.ntiles * items < CONV_SINGLE_BLOCKS) {
+  const long long two = (long long)b.nouter * b.ntiles * items, one = 2LL * b.n1 * b.ntiles * items;
+  auto rounds = [resident](long long blocks) { return (blocks + resident - 1) / resident; };
+  if (b.ntail == 0 && two < CONV_SINGLE_BLOCKS && rounds(one) < 2 * rounds(two)) {
     b.single = 1;
     b.nouter = 2 * b.n1;
   }
@@ -315,22 +332,12 @@ hipError_t launch_col(int L, int v, int kind, const ColArgs& a, int items, hipSt
         hipLaunchKernelGGL((k_col_conv_pipe<T, LV, cc.pid, cc.tiles, cc.nq>), dim3(nb, items),      \
                            dim3(cc.tiles * cc.nq), 0, s, b);                                        \
       } else {                                                                                      \
-        const ColArgs b = conv_single(conv_gather(a, cc.tiles), items);                             \
-        const dim3 gridc((unsigned)(b.nouter * b.ntiles + b.ntail), (unsigned)items);               \
-        if constexpr (conv_twf<T>(LV, VV) && conv_split_wpe<T>(LV) > 0)                            \
-          hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, true, 0, true,             \
-                                         conv_split_wpe<T>(LV)>),                                   \
-                             gridc, dim3(cc.tiles * cc.nq), 0, s, b);                               \
-        else if constexpr (conv_twf<T>(LV, VV))                                                     \
-          hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, true>), gridc,             \
-                             dim3(cc.tiles * cc.nq), 0, s, b);                                      \
-        else if constexpr (VV == 0 && conv_split_wpe<T>(LV) > 0)                                    \
-          hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, false, 0, true,            \
-                                         conv_split_wpe<T>(LV)>),                                   \
-                             gridc, dim3(cc.tiles * cc.nq), 0, s, b);                               \
-        else                                                                                        \
-          hipLaunchKernelGGL((k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq>), gridc,                   \
-                             dim3(cc.tiles * cc.nq), 0, s, b);                                      \
+        constexpr bool tf = conv_twf<T>(LV, VV);                                                    \
+        constexpr int sw = tf || VV == 0 ? conv_split_wpe<T>(LV) : 0;                               \
+        constexpr auto* kernel = &k_col_conv<T, LV, cc.pid, cc.tiles, cc.nq, tf, 0, (sw > 0), (sw > 0 ? sw : 1)>; \
+        const ColArgs b = conv_single(conv_gather(a, cc.tiles), items, resident_blocks<kernel>(cc.tiles * cc.nq)); \
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(b.nouter * b.ntiles + b.ntail), (unsigned)items), \
+                           dim3(cc.tiles * cc.nq), 0, s, b);                                        \
       }                                                                                             \
     } else if (kind == 1)                                                                           \
       hipLaunchKernelGGL((k_col_fft<T, LV, c.pid, c.tiles, c.nq, true>), grid, block, 0, s, a);     \

@@ -1,6 +1,7 @@
-"""float64 launch groups with spectra of up to 32 MB stream past the caches: a solve
-alone and in groups on both sides of that line keeps its bits, and is the
-oracle's."""
+"""Small launches choose where they store (float64 spectra of up to 32 MB a launch
+stream past the caches) and how many blocks the axis-0 pass takes (one or two
+pencil sets a block, by rounds of resident blocks): a solve alone and in groups
+on both sides of these lines keeps its bits, and is the oracle's."""
 from __future__ import annotations
 
 import numpy as np
@@ -37,3 +38,29 @@ def test_groups_keep_a_solves_bits(n, prec, tol, etol):
         for count in (2, 3, 5, 8, 12, 16):
             for a, b in zip(alone, solve_batched(plans[:count], rhos[:count])):
                 assert torch.equal(a, b), (schedule, count)
+
+
+def test_first_launch_under_capture():
+    """The axis-0 pass asks the runtime for its resident blocks on its first launch, here inside a
+    capture, in a process of its own."""
+    import os
+    import subprocess
+    import sys
+
+    code = """
+import sys; sys.path.insert(0, %r)
+import torch
+from paper_2405_02603_amd import Batch, Plan
+for prec, dtype in (("f32", torch.float32), ("f64", torch.float64)):
+    plans = [Plan(n=(96, 24, 24), greens="hockney", prec=prec) for _ in range(3)]
+    rhos = [torch.randn(96, 24, 24, device="cuda", dtype=dtype) for _ in plans]
+    batch = Batch(plans, rhos)
+    for _ in range(3):
+        batch.launch()
+    torch.cuda.synchronize()
+    for p, r, o in zip(plans, rhos, batch.outs):
+        assert torch.equal(p.solve(r), o)
+print("captured")
+""" % os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0 and "captured" in run.stdout, run.stderr[-2000:]
